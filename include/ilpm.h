@@ -15,7 +15,10 @@
  *       + sum_{ci<C_in, kh<K, kw<K} w[co][ci][kh][kw] * x[ci][oh*s - p + kh][ow*s - p + kw]
  *   (x read as 0 outside [0,H) x [0,W)).
  *
- * Arithmetic is fp32 in, fp32 accumulate (fp32 FMA or fp32 MFMA), fp32 out.
+ * Arithmetic is fp32 in, fp32 accumulate, fp32 out: fp32 FMA, fp32 MFMA, or
+ * bf16 MFMA on operands split into three bf16 parts each (24 significand bits;
+ * six products with fp32 accumulation in place of one, closer to the exact sum
+ * than an fp32 chain).
  * The summation order is not the definition's; results agree with the exact
  * sum to within 1e-4 * (1 + S / (C_in*K*K)), S = sum of |products|.
  *
@@ -60,8 +63,9 @@ enum {
 enum {
     ILPM_PATH_DIRECT = 0, /* VALU direct convolution: lanes on output pixels, a
                              block of output channels per thread, taps outermost */
-    ILPM_PATH_IGEMM = 1   /* fp32-MFMA implicit GEMM: M = C_out, N = output pixels,
-                             K = C_in*K*K, input halo tiles staged in LDS */
+    ILPM_PATH_IGEMM = 1   /* MFMA implicit GEMM: M = C_out, N = output pixels,
+                             K = C_in*K*K, input halo tiles staged in LDS; on fp32
+                             operands, or ("_b3_" variants) on bf16 parts of them */
 };
 
 /* How one call is executed (see ilpm_conv2d_plan). */
@@ -93,7 +97,9 @@ typedef struct ilpm_plan {
  * array of tile arrival counts that the library holds; calls that overlap in
  * time on one device and both use split plans must be ordered on one stream.
  * Workspace: the one registered with ilpm_set_workspace (ILPM_ERR_WORKSPACE
- * if it is too small), else the library's own for the current device.  A
+ * if it is too small), else the library's own for the current device.  (Where
+ * a bf16-split default plan finds no room for its partial sums, the fp32
+ * variants' plan runs instead, and only what that one needs can be refused.)  A
  * call that needs more than the library's own holds allocates a larger one
  * (hipMalloc: no synchronisation, no free -- the smaller buffer is kept
  * until the process ends, because work already enqueued or a HIP graph
@@ -189,7 +195,7 @@ int ilpm_conv2d_validate(const void *in, const void *w, const void *bias,
  * ilpm_conv2d_plan -- the plan ilpm_conv2d_fwd uses for this shape (path,
  * tile, split count, grid, workspace): the fastest plan measured on MI355X
  * for this exact shape when the compiled-in tuning table lists it, else the
- * best by a cost model.  Pure host.  A shape's plan is chosen once and kept
+ * best by cost models fitted to measured times.  Pure host.  A shape's plan is chosen once and kept
  * (a table in the library), so later calls cost a lookup.
  * Environment overrides, read once, the first time the library plans a call
  * (for sweeps and ablations; any of them bypasses the tuning table):
@@ -222,7 +228,9 @@ const char *ilpm_variant_name(int path, int variant);
 
 /*
  * ilpm_variant_info -- filter size, stride (0 = any), output tile and output
- * channels per workgroup of one compiled variant.  Pure host.
+ * channels per workgroup of one compiled variant.  Pure host.  A bf16-split
+ * ("_b3_") variant names its usual tile here; each plan's tile is chosen for
+ * its shape.  Its 1x1 variants take any stride.
  */
 int ilpm_variant_info(int path, int variant, int *K, int *stride, int *tile_h, int *tile_w,
                       int *co_tile);

@@ -96,6 +96,15 @@ struct IgArgs {
     int pool_tile;  // out is the 2x2 max-pooled output, pooled in the workgroup (PoolTile)
 };
 
+// The output tile of a bf16-split plan (conv_split.h), chosen per shape.
+struct SplitTile {
+    int th, tw;
+    int step;        // input pixels between halo pixels: 1, for 1x1 filters the stride
+    FastDiv tw_d;    // by TW (in-kernel pooling: by TW / 2)
+    FastDiv hc_d;    // by the halo's columns
+    FastDiv npix_d;  // by the halo's pixels
+};
+
 // One compiled kernel variant: its configuration and a launcher.
 struct Variant {
     const char *name;
@@ -109,6 +118,18 @@ struct Variant {
     bool c1;        // consecutive channels per lane (Cfg::C1): plans need C_in a multiple of 4
     void (*launch)(dim3 grid, hipStream_t st, const float *, const float *, const float *, float *, float *,
                    const IgArgs &, bool packed);
+    // bf16-split variants (conv_split.h): th and tw above are only what
+    // variant_info names, a plan's tile is chosen for its shape.
+    void (*launch3)(dim3 grid, hipStream_t st, const float *, const float *, const float *, float *, float *,
+                    const IgArgs &, const SplitTile &, bool packed) = nullptr;
+    int px = 0, xpix = 0;  // most output and halo pixels of a tile
+    bool even = false;     // tiles with even sides: a 2x2 max-pool stays in the kernel
+    // Measured times, us, of igemm_plan_us (see there).
+    struct Times {
+        double base, stage1, stage2, round, out, part, split;
+    };
+    int per_cu = 1;  // workgroups a compute unit holds
+    Times us = {};
 };
 
 // The variant table, in parts (conv_igemm_v*.hip): each sets *table and
@@ -124,6 +145,9 @@ int variants_part7(const Variant **table);
 int variants_part8(const Variant **table);
 int variants_part9(const Variant **table);
 int variants_part10(const Variant **table);
+int variants_split0(const Variant **table);
+int variants_split1(const Variant **table);
+int variants_split2(const Variant **table);
 
 }  // namespace ig
 
@@ -133,6 +157,7 @@ using ig::fast_div;
 using ig::FastDiv;
 using ig::IgArgs;
 using ig::make_fastdiv;
+using ig::SplitTile;
 using ig::Variant;
 
 

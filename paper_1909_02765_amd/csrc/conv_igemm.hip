@@ -2,6 +2,7 @@
 // plans and their cost model, launches, and the kernels that sum split
 // partial outputs and pack weights.  The kernel templates and the algorithm's
 // description are in conv_igemm.h.
+#include <algorithm>
 #include <atomic>
 #include <vector>
 
@@ -132,6 +133,25 @@ struct PackGeom {
     int c1;  // consecutive channels per lane (Cfg::C1)
 };
 
+// The prepacked layout of a bf16-split variant: per (output-channel tile,
+// channel chunk) [tap][8-channel group][half][output channel][4 channels]; one
+// thread per packed float.
+__global__ __launch_bounds__(256) void pack_split_weights(const float *__restrict__ w, float *__restrict__ packed,
+                                                          int c_in, int c_out, int kk, int cot, int cc, int nchunks,
+                                                          int64_t total)
+{
+    const int64_t step = (int64_t)gridDim.x * 256;
+    for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += step) {
+        const int64_t block = idx / (cot * cc * kk);
+        const int within = (int)(idx - block * (cot * cc * kk));
+        const int e = within % 4, r = within / (4 * cot);
+        const int tap = r / (cc / 4);
+        const int co = (int)(block / nchunks) * cot + within / 4 % cot;
+        const int ci = (int)(block % nchunks) * cc + r % (cc / 4) * 4 + e;
+        packed[idx] = (co < c_out && ci < c_in) ? w[((int64_t)co * c_in + ci) * kk + tap] : 0.f;
+    }
+}
+
 __global__ __launch_bounds__(256) void pack_weights(const float *__restrict__ w, float *__restrict__ packed,
                                                     PackGeom g, int64_t total)
 {
@@ -171,7 +191,8 @@ const std::vector<const Variant *> &variant_table()
         int (*const parts[])(const Variant **) = {ig::variants_part0, ig::variants_part1, ig::variants_part2,
                                                   ig::variants_part3, ig::variants_part4, ig::variants_part5,
                                                   ig::variants_part6, ig::variants_part7, ig::variants_part8,
-                                                  ig::variants_part9, ig::variants_part10};
+                                                  ig::variants_part9, ig::variants_part10, ig::variants_split0,
+                                                  ig::variants_split1, ig::variants_split2};
         std::vector<const Variant *> t;
         for (auto part : parts) {
             const Variant *v = nullptr;
@@ -187,6 +208,59 @@ const Variant &variant_at(int v) { return *variant_table()[v]; }
 int num_variants() { return (int)variant_table().size(); }
 
 constexpr int kCUs = 256;
+
+// Halo pixels along one axis of `n` output pixels (1x1 filters load only the
+// pixels they use).
+int halo_extent(int n, int k, int s) { return k == 1 ? n : (n - 1) * s + k; }
+
+// The tile of a bf16-split plan: of the tiles of at most px output and xpix
+// halo pixels, one with the fewest tiles over the output (every tile costs the
+// same, full or not), rows of 16 pixels (whole 64-byte stores) worth a tenth
+// more tiles (64->64 at 224^2: 15x14-pixel tiles took 6 us more to store the
+// output than 16x16-pixel ones); then the smallest halo.
+bool split_tile(const ConvShape &s, const Variant &d, int *th_out, int *tw_out)
+{
+    struct Memo {
+        const Variant *d = nullptr;
+        int ho, wo, th, tw;
+    };
+    thread_local Memo memo[64];
+    Memo &e = memo[((unsigned)s.h_out * 31u + (unsigned)s.w_out * 7u + (unsigned)((uintptr_t)&d / sizeof(Variant))) % 64];
+    if (e.d == &d && e.ho == s.h_out && e.wo == s.w_out) {
+        *th_out = e.th;
+        *tw_out = e.tw;
+        return e.th > 0;
+    }
+    const int step = d.even ? 2 : 1;
+    int best_th = 0, best_tw = 0;
+    int64_t best = 0;
+    for (int tw = step; tw <= d.px && tw < s.w_out + step; tw += step) {
+        const int hc = halo_extent(tw, s.k, s.stride);
+        int th = std::min(d.px / tw, s.h_out + step - 1);
+        while (th > 0 && halo_extent(th, s.k, s.stride) * hc > d.xpix) --th;
+        th = th / step * step;
+        if (th <= 0) continue;
+        // The same number of tiles with sides as equal as can be.
+        const int nh = ceil_div(s.h_out, th), nw = ceil_div(s.w_out, tw);
+        th = ceil_div(ceil_div(s.h_out, nh), step) * step;
+        if (ceil_div(ceil_div(s.w_out, nw), step) * step != tw) continue;  // a narrower tile does the same
+        const int64_t cost = (int64_t)nh * nw * (tw % 16 == 0 ? 10 : 11) * 65536 +
+                             halo_extent(th, s.k, s.stride) * hc;
+        if (best_th == 0 || cost < best) {
+            best = cost;
+            best_th = th;
+            best_tw = tw;
+        }
+    }
+    e.d = &d;
+    e.ho = s.h_out;
+    e.wo = s.w_out;
+    e.th = best_th;
+    e.tw = best_tw;
+    *th_out = best_th;
+    *tw_out = best_tw;
+    return best_th > 0;
+}
 
 }  // namespace
 
@@ -222,7 +296,7 @@ bool igemm_make_plan(const ConvShape &s, int variant, int splits, ilpm_plan *p)
 {
     if (variant < 0 || variant >= num_variants()) return false;
     const Variant &d = variant_at(variant);
-    if (d.ks != s.k || d.s != s.stride) return false;
+    if (d.ks != s.k || (d.s != s.stride && !(d.launch3 && d.ks == 1))) return false;
     // Consecutive channels per lane: 16-byte weight loads that stay inside
     // the tensor only when C_in is a multiple of 4.
     if (d.c1 && s.c_in % 4 != 0) return false;
@@ -237,7 +311,9 @@ bool igemm_make_plan(const ConvShape &s, int variant, int splits, ilpm_plan *p)
     if (s.h >= (1 << 23) || s.w >= (1 << 23) || s.h_out >= (1 << 23) || s.w_out >= (1 << 23)) return false;
     // A stage's channels (up to CC, past C_in too) stay within 31-bit offsets.
     if ((int64_t)(s.c_in > d.cc ? s.c_in : d.cc) * s.h * s.w * 4 >= (1LL << 31)) return false;
-    const long tiles = (long)ceil_div(s.h_out, d.th) * ceil_div(s.w_out, d.tw) * ceil_div(s.c_out, d.cot);
+    int th = d.th, tw = d.tw;
+    if (d.launch3 && !split_tile(s, d, &th, &tw)) return false;
+    const long tiles = (long)ceil_div(s.h_out, th) * ceil_div(s.w_out, tw) * ceil_div(s.c_out, d.cot);
     if (tiles > 0x7fffffffL) return false;
     const int nchunks = ceil_div(s.c_in, d.cc);
     if (splits <= 0) {
@@ -262,8 +338,8 @@ bool igemm_make_plan(const ConvShape &s, int variant, int splits, ilpm_plan *p)
     ilpm_plan q = {};
     q.path = ILPM_PATH_IGEMM;
     q.variant = variant;
-    q.tile_h = d.th;
-    q.tile_w = d.tw;
+    q.tile_h = th;
+    q.tile_w = tw;
     q.co_tile = d.cot;
     q.ci_chunk = d.cc;
     q.splits = splits;
@@ -274,6 +350,38 @@ bool igemm_make_plan(const ConvShape &s, int variant, int splits, ilpm_plan *p)
     q.w_out = s.w_out;
     q.workspace_bytes = splits > 1 ? sizeof(float) * out_elems * splits : 0;
     *p = q;
+    return true;
+}
+
+// Time of the second pass of a split or pooled plan by the same fits: a launch
+// and the partial sums out and in again.
+double igemm_plan_us(const ConvShape &s, const ilpm_plan &p, bool pooled)
+{
+    const Variant &d = variant_at(p.variant);
+    const double out_mb = 4e-6 * s.c_out * s.h_out * s.w_out;
+    const bool second = p.splits > 1 || (pooled && !(d.poolable && p.splits == 1));
+    if (!d.launch3) {
+        // The cycle model, at 2.4 GHz: within 20% of the measured time on
+        // these layers but for 1x1 filters, where it was 0-40% short.
+        double us = igemm_plan_cost(s, p) / 2400.0 * (s.k == 1 ? 1.2 : 1.0);
+        if (pooled && second && p.splits == 1) us += 1.7 + 0.2 * out_mb * 2.0;
+        return us;
+    }
+    // A compute unit runs its workgroups `per_cu` at a time; a stage of two
+    // together takes stage2, of one alone stage1.
+    const int stages = ceil_div(ceil_div(s.c_in, d.cc), p.splits);
+    const int per = ceil_div(p.grid, kCUs);
+    const int pairs = d.per_cu == 2 ? per / 2 : 0, singles = per - 2 * pairs;
+    double us = d.us.base + (pairs + singles) * d.us.round + stages * (pairs * d.us.stage2 + singles * d.us.stage1);
+    if (second) us += d.us.split + d.us.part * out_mb * (2 * p.splits + 1);
+    else us += d.us.out * out_mb * (pooled ? 0.25 : 1.0);
+    return us;
+}
+
+bool igemm_is_split(int variant, bool *even)
+{
+    if (variant < 0 || variant >= num_variants() || !variant_at(variant).launch3) return false;
+    *even = variant_at(variant).even;
     return true;
 }
 
@@ -330,6 +438,11 @@ hipError_t igemm_pack(const ilpm_plan &p, int c_in, int c_out, const float *w, f
     const int64_t total = igemm_packed_floats(p, c_in, c_out);
     int64_t blocks = (total + 255) / 256;
     if (blocks > 65536) blocks = 65536;
+    if (d.launch3) {
+        hipLaunchKernelGGL(pack_split_weights, dim3((unsigned)blocks), dim3(256), 0, stream, w, packed, c_in, c_out,
+                           g.kk, d.cot, d.cc, g.nchunks, total);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(pack_weights, dim3((unsigned)blocks), dim3(256), 0, stream, w, packed, g, total);
     return hipGetLastError();
 }
@@ -370,8 +483,8 @@ hipError_t igemm_launch(const ilpm_plan &p, const ConvShape &s, const float *x, 
     a.chunks_per_split = ceil_div(a.nchunks, p.splits);
     a.ntiles = make_fastdiv((unsigned)(p.grid / p.splits));
     a.co_tiles = make_fastdiv((unsigned)ceil_div(s.c_out, d.cot));
-    a.tiles_w = make_fastdiv((unsigned)ceil_div(s.w_out, d.tw));
-    a.sp_tiles = make_fastdiv((unsigned)(ceil_div(s.h_out, d.th) * ceil_div(s.w_out, d.tw)));
+    a.tiles_w = make_fastdiv((unsigned)ceil_div(s.w_out, p.tile_w));
+    a.sp_tiles = make_fastdiv((unsigned)(ceil_div(s.h_out, p.tile_h) * ceil_div(s.w_out, p.tile_w)));
     // Each XCD runs a contiguous run of workgroups.  When the weights
     // outweigh the input, let the run share output-channel tiles (and so
     // weights) across spatial tiles; otherwise share spatial tiles (input).
@@ -384,13 +497,24 @@ hipError_t igemm_launch(const ilpm_plan &p, const ConvShape &s, const float *x, 
     a.relu = relu ? 1 : 0;
     const int tiles = p.grid / p.splits;
     a.splits = p.splits;
-    a.fuse = (p.splits > 1 && !pool && tiles <= kMaxFusedTiles &&
+    a.fuse = (!d.launch3 && p.splits > 1 && !pool && tiles <= kMaxFusedTiles &&
               ceil_div(d.cot * d.th * d.tw, d.nt) * p.splits <= kFuseMaxLoads &&
               g_split_sum_mode.load(std::memory_order_relaxed) == ILPM_SPLIT_SUM_FUSED)
                  ? 1
                  : 0;
     float *part = static_cast<float *>(workspace);
-    d.launch(dim3(tiles * p.splits), stream, x, w, bias, out, part, a, packed);
+    if (d.launch3) {
+        SplitTile t;
+        t.th = p.tile_h;
+        t.tw = p.tile_w;
+        t.step = s.k == 1 ? s.stride : 1;
+        t.tw_d = make_fastdiv((unsigned)(a.pool_tile ? t.tw / 2 : t.tw));
+        t.hc_d = make_fastdiv((unsigned)halo_extent(t.tw, s.k, s.stride));
+        t.npix_d = make_fastdiv((unsigned)(halo_extent(t.tw, s.k, s.stride) * halo_extent(t.th, s.k, s.stride)));
+        d.launch3(dim3(tiles * p.splits), stream, x, w, bias, out, part, a, t, packed);
+    } else {
+        d.launch(dim3(tiles * p.splits), stream, x, w, bias, out, part, a, packed);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !a.to_part || a.fuse) return e;
     if (pool) {

@@ -134,15 +134,19 @@ int validate(const void *in, const void *w, const void *bias, const ConvShape &s
 // the cheapest matrix-core variant for this filter size and stride by the
 // cost model, else the LDS direct kernel, else the plain one.  The
 // environment overrides (read once) narrow the candidates.
-int compute_plan(const ConvShape &s, ilpm_plan *p, bool prepacked, bool pooled)
+// base: without the bf16-split variants (conv_split.h).
+int compute_base_plan(const ConvShape &s, ilpm_plan *p, bool prepacked, bool pooled, bool *tuned)
 {
     const Overrides &o = overrides();
     const bool any = o.path < 0 && o.splits == 0 && o.tile_h == 0;
+    *tuned = false;
     if (any) {
+        *tuned = true;
         if (pooled && prepacked && tuned_plan(s, p, true, true)) return ILPM_OK;
         if (prepacked && tuned_plan(s, p, true, false)) return ILPM_OK;
         if (pooled && tuned_plan(s, p, false, true)) return ILPM_OK;
         if (tuned_plan(s, p, false, false)) return ILPM_OK;
+        *tuned = false;
     }
     auto tile_ok = [&](const ilpm_plan &q) { return o.tile_h == 0 || (q.tile_h == o.tile_h && q.tile_w == o.tile_w); };
     if (o.path != ILPM_PATH_DIRECT) {
@@ -151,7 +155,8 @@ int compute_plan(const ConvShape &s, ilpm_plan *p, bool prepacked, bool pooled)
         ilpm_plan bp = {};
         for (int v = 0; v < igemm_num_variants(); ++v) {
             ilpm_plan q;
-            if (!igemm_make_plan(s, v, o.splits, &q) || !tile_ok(q)) continue;
+            bool even;
+            if (igemm_is_split(v, &even) || !igemm_make_plan(s, v, o.splits, &q) || !tile_ok(q)) continue;
             const double c = igemm_plan_cost(s, q);
             if (!found || c < best) {
                 found = true;
@@ -175,12 +180,47 @@ int compute_plan(const ConvShape &s, ilpm_plan *p, bool prepacked, bool pooled)
     return ILPM_ERR_UNSUPPORTED;
 }
 
+// The base plan, or for a shape that no table lists the bf16-split plan with
+// the shortest modelled time, where that is at most 0.95 times the base
+// plan's.  Against a direct (VALU) plan, which has no model, a bf16-split one
+// is taken from 16 input channels on: with fewer most of its 16-, 64- or
+// 8-channel stage is padding and the low-channel matrix-core kernels or the
+// VALU kernel's first-layer shapes are near (measured, from a graph: 1x1
+// stride 2 64->128 at 112^2 83.6 us direct, 5.7 bf16-split; 5x5 stride 2
+// 32->64 at 224^2 124 us, 20.7).  A plan that needs more than the no-alloc
+// array keeps to the base plan, so that the no-alloc call goes on taking it.
+int compute_plan(const ConvShape &s, ilpm_plan *p, bool prepacked, bool pooled)
+{
+    bool tuned;
+    const int rc = compute_base_plan(s, p, prepacked, pooled, &tuned);
+    const Overrides &o = overrides();
+    if (tuned || o.path >= 0 || o.splits > 0 || o.tile_h > 0) return rc;
+    const bool direct = rc == ILPM_OK && p->path == ILPM_PATH_DIRECT;
+    if (direct && (direct_is_lowc(p->variant) || s.c_in < 16)) return rc;
+    double best = rc == ILPM_OK && !direct ? 0.95 * igemm_plan_us(s, *p, pooled) : 1e30;
+    for (int v = 0; v < igemm_num_variants(); ++v) {
+        bool even;
+        if (!igemm_is_split(v, &even) || (even && !pooled)) continue;
+        for (int splits : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
+            ilpm_plan q;
+            if (!igemm_make_plan(s, v, splits, &q) || q.splits != splits) continue;
+            if (igemm_workspace_bytes(q, s, 0) > ILPM_NOALLOC_SCRATCH_BYTES) continue;
+            const double us = igemm_plan_us(s, q, pooled);
+            if (us < best) {
+                best = us;
+                *p = q;
+            }
+        }
+    }
+    return best < 1e30 ? ILPM_OK : rc;
+}
+
 // Plans already chosen, by shape: a direct-mapped table, so a call on a shape
 // seen before costs one hash and one comparison instead of the table scan and
 // the cost-model sweep.
 struct PlanSlot {
     bool used = false;
-    int mode;  // 1: prepacked weights, 2: pooled epilogue
+    int mode;  // 1: prepacked weights, 2: pooled epilogue, 4: base plan
     ConvShape s;
     int rc;
     ilpm_plan p;
@@ -194,9 +234,10 @@ bool same_shape(const ConvShape &a, const ConvShape &b)
            a.stride == b.stride && a.pad == b.pad;
 }
 
-int choose_plan(const ConvShape &s, ilpm_plan *p, bool prepacked = false, bool pooled = false)
+// base: the plan without the bf16-split variants (compute_base_plan).
+int choose_plan(const ConvShape &s, ilpm_plan *p, bool prepacked = false, bool pooled = false, bool base = false)
 {
-    const int mode = (prepacked ? 1 : 0) | (pooled ? 2 : 0);
+    const int mode = (prepacked ? 1 : 0) | (pooled ? 2 : 0) | (base ? 4 : 0);
     uint64_t h = 1469598103934665603ull;  // FNV-1a over the seven sizes and the mode
     for (int v : {s.c_in, s.h, s.w, s.c_out, s.k, s.stride, s.pad, mode})
         h = (h ^ (uint32_t)v) * 1099511628211ull;
@@ -209,7 +250,8 @@ int choose_plan(const ConvShape &s, ilpm_plan *p, bool prepacked = false, bool p
         }
     }
     ilpm_plan q = {};
-    const int rc = compute_plan(s, &q, prepacked, pooled);
+    bool tuned;
+    const int rc = base ? compute_base_plan(s, &q, prepacked, pooled, &tuned) : compute_plan(s, &q, prepacked, pooled);
     std::lock_guard<std::mutex> lk(g_mu);
     slot.used = true;
     slot.mode = mode;
@@ -370,6 +412,29 @@ int run(const float *in, const float *w, const float *bias, const ConvShape &s, 
         e = direct_launch(p, s, in, w, bias, out, stream, relu);
     }
     return e == hipSuccess ? ILPM_OK : hip_fail(e);
+}
+
+// A call with the shape's default plan.  Where that is a bf16-split plan whose
+// partial sums find no room (a registered workspace that is too small, a
+// capture that may not allocate, the no-alloc array), the base plan runs
+// instead: what it needs decides whether the call is refused.
+int run_default(const float *in, const float *w, const float *bias, const ConvShape &s, float *out,
+                hipStream_t stream, int epilogue = 0, bool use_scratch = false)
+{
+    const bool pooled = (epilogue & ILPM_EPI_MAXPOOL2) != 0;
+    ilpm_plan p;
+    int rc = choose_plan(s, &p, false, pooled);
+    if (rc != ILPM_OK) return rc;
+    auto go = [&] {
+        if (use_scratch && workspace_need(p, s, epilogue) > ILPM_NOALLOC_SCRATCH_BYTES) return (int)ILPM_ERR_WORKSPACE;
+        return run(in, w, bias, s, out, p, stream, false, epilogue, use_scratch);
+    };
+    rc = go();
+    bool even;
+    if (rc == ILPM_ERR_WORKSPACE && p.path == ILPM_PATH_IGEMM && igemm_is_split(p.variant, &even) &&
+        choose_plan(s, &p, false, pooled, true) == ILPM_OK)
+        rc = go();
+    return rc;
 }
 
 // Bytes of the prepacked weights of plan p (0 with *rc set on a bad plan).
@@ -564,10 +629,7 @@ int ilpm_conv2d_fwd(const float *in, const float *w, const float *bias, int C_in
     if (rc != ILPM_OK) return rc;
     rc = validate(in, w, bias, s, out);
     if (rc != ILPM_OK) return rc;
-    ilpm_plan p;
-    rc = choose_plan(s, &p);
-    if (rc != ILPM_OK) return rc;
-    return run(in, w, bias, s, out, p, stream);
+    return run_default(in, w, bias, s, out, stream);
 }
 
 int ilpm_arch_supported(const char *gcn_arch_name) { return arch_status(gcn_arch_name); }
@@ -580,11 +642,7 @@ int ilpm_conv2d_fwd_noalloc(const float *in, const float *w, const float *bias, 
     if (rc != ILPM_OK) return rc;
     rc = validate(in, w, bias, s, out);
     if (rc != ILPM_OK) return rc;
-    ilpm_plan p;
-    rc = choose_plan(s, &p);
-    if (rc != ILPM_OK) return rc;
-    if (workspace_need(p, s, 0) > ILPM_NOALLOC_SCRATCH_BYTES) return ILPM_ERR_WORKSPACE;
-    return run(in, w, bias, s, out, p, stream, false, 0, true);
+    return run_default(in, w, bias, s, out, stream, 0, true);
 }
 
 int ilpm_conv2d_fwd_plan(const float *in, const float *w, const float *bias, int C_in, int H, int W, int C_out,
@@ -682,15 +740,10 @@ int ilpm_conv2d_fwd_epilogue(const float *in, const float *w, const float *bias,
     if ((epilogue & ILPM_EPI_MAXPOOL2) && (s.h_out < 2 || s.w_out < 2)) return ILPM_ERR_INVALID_ARG;
     rc = validate(in, w, bias, s, out, epilogue);
     if (rc != ILPM_OK) return rc;
-    ilpm_plan p;
-    if (plan) {
-        rc = check_plan(s, *plan);
-        p = *plan;
-    } else {
-        rc = choose_plan(s, &p, false, (epilogue & ILPM_EPI_MAXPOOL2) != 0);
-    }
+    if (!plan) return run_default(in, w, bias, s, out, stream, epilogue);
+    rc = check_plan(s, *plan);
     if (rc != ILPM_OK) return rc;
-    return run(in, w, bias, s, out, p, stream, false, epilogue);
+    return run(in, w, bias, s, out, *plan, stream, false, epilogue);
 }
 
 int ilpm_winograd_filter_size(int C_in, int C_out, size_t *bytes)

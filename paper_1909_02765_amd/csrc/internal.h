@@ -37,6 +37,12 @@ bool igemm_make_plan(const ConvShape &s, int variant, int splits, ilpm_plan *p);
 // Modelled cost of a plan in SIMD cycles of the slowest compute unit, used to
 // rank variants; lower is better.
 double igemm_plan_cost(const ConvShape &s, const ilpm_plan &p);
+// Modelled time of a plan in us, comparable between the fp32 and the
+// bf16-split variants (pooled: with the ReLU + 2x2 max-pool epilogue).
+double igemm_plan_us(const ConvShape &s, const ilpm_plan &p, bool pooled);
+// Whether a variant is a bf16-split one (conv_split.h), and then whether its
+// tiles have even sides (the 2x2 max-pool stays in the kernel).
+bool igemm_is_split(int variant, bool *even);
 // packed: w is in the variant's prepacked layout (igemm_pack) instead of OIHW.
 // epilogue: ILPM_EPI_* bits.  With ILPM_EPI_MAXPOOL2, out is the pooled
 // [C_out][H_out/2][W_out/2] tensor and the workspace holds every split's
