@@ -19,6 +19,8 @@
 //            conv_direct_mfma below.
 #include "internal.h"
 
+#include <algorithm>
+
 namespace ilpm {
 namespace {
 
@@ -509,8 +511,8 @@ __global__ __launch_bounds__(256) void conv_direct_rows(const float *__restrict_
     if (!active) return;  // no barrier follows
 
     // A: this lane's weights w[co0 + l][4s + g] (read for every slot: the
-    // word a slot past C_in*K*K would read lies inside the weight and bias
-    // areas); the accumulators start at the bias.
+    // word a slot past C_in*K*K would read lies inside the weight area or
+    // the rows_slack words behind it); the accumulators start at the bias.
     float av[STEPS];
 #pragma unroll
     for (int s = 0; s < STEPS; ++s) {
@@ -573,18 +575,18 @@ __global__ __launch_bounds__(256) void conv_direct_rows(const float *__restrict_
 
 struct RowsVariant {
     const char *name;
-    int nb, pw, cw;
+    int nb, pw, cw, steps;
     void (*launch)(dim3, int, hipStream_t, const float *, const float *, const float *, float *, const RowsArgs &);
 };
 
-template <int NB, int PW, int CW, int POL>
+template <int NB, int PW, int CW, int STEPS, int POL>
 void rows_launch(dim3 grid, int lds, hipStream_t st, const float *x, const float *w, const float *b, float *o,
                  const RowsArgs &a)
 {
     if (a.stride == 1)
-        hipLaunchKernelGGL((conv_direct_rows<NB, PW, CW, 7, POL, 1>), grid, dim3(256), lds, st, x, w, b, o, a);
+        hipLaunchKernelGGL((conv_direct_rows<NB, PW, CW, STEPS, POL, 1>), grid, dim3(256), lds, st, x, w, b, o, a);
     else
-        hipLaunchKernelGGL((conv_direct_rows<NB, PW, CW, 7, POL, 0>), grid, dim3(256), lds, st, x, w, b, o, a);
+        hipLaunchKernelGGL((conv_direct_rows<NB, PW, CW, STEPS, POL, 0>), grid, dim3(256), lds, st, x, w, b, o, a);
 }
 
 // Store policy SC1 (device scope): the output is written through each XCD's
@@ -594,19 +596,42 @@ void rows_launch(dim3 grid, int lds, hipStream_t st, const float *x, const float
 // measured faster with it than with ordinary stores.
 constexpr int kSc1 = 16;
 
+// k76 and k148: 19 and 37 matrix steps, for contractions of up to 3 channels
+// of a 5x5 or 7x7 filter.  A workgroup reads each input row once per filter
+// row and each weight once, so what bounds it is its start: the row and weight
+// DMAs and the LDS latency of the first operands (7x7 stride 2 3->64 at 224^2:
+// 0.24 GF and 3.9 MB, 0.8 us of copying; 9.0 us from a graph, where the VALU
+// kernel that ran it before takes 22.2).  Smaller channel groups where C_out
+// is small, longer segments where the grid fills the chip anyway.
 const RowsVariant kRows[] = {
-    {"direct_rows_k28_co64_px224_sc1", 14, 1, 4, &rows_launch<14, 1, 4, kSc1>},
-    {"direct_rows_k28_co64_px112_sc1", 7, 1, 4, &rows_launch<7, 1, 4, kSc1>},
-    {"direct_rows_k28_co64_px64_sc1", 4, 1, 4, &rows_launch<4, 1, 4, kSc1>},
-    {"direct_rows_k28_co64_px32_sc1", 2, 1, 4, &rows_launch<2, 1, 4, kSc1>},
-    {"direct_rows_k28_co32_px128_sc1", 4, 2, 2, &rows_launch<4, 2, 2, kSc1>},
-    {"direct_rows_k28_co32_px32_sc1", 1, 2, 2, &rows_launch<1, 2, 2, kSc1>},
-    {"direct_rows_k28_co16_px64_sc1", 1, 4, 1, &rows_launch<1, 4, 1, kSc1>},
-    {"direct_rows_k28_co16_px32_sc1", 1, 2, 1, &rows_launch<1, 2, 1, kSc1>},
+    {"direct_rows_k28_co64_px224_sc1", 14, 1, 4, 7, &rows_launch<14, 1, 4, 7, kSc1>},
+    {"direct_rows_k28_co64_px112_sc1", 7, 1, 4, 7, &rows_launch<7, 1, 4, 7, kSc1>},
+    {"direct_rows_k28_co64_px64_sc1", 4, 1, 4, 7, &rows_launch<4, 1, 4, 7, kSc1>},
+    {"direct_rows_k28_co64_px32_sc1", 2, 1, 4, 7, &rows_launch<2, 1, 4, 7, kSc1>},
+    {"direct_rows_k28_co32_px128_sc1", 4, 2, 2, 7, &rows_launch<4, 2, 2, 7, kSc1>},
+    {"direct_rows_k28_co32_px32_sc1", 1, 2, 2, 7, &rows_launch<1, 2, 2, 7, kSc1>},
+    {"direct_rows_k28_co16_px64_sc1", 1, 4, 1, 7, &rows_launch<1, 4, 1, 7, kSc1>},
+    {"direct_rows_k28_co16_px32_sc1", 1, 2, 1, 7, &rows_launch<1, 2, 1, 7, kSc1>},
+    {"direct_rows_k76_co64_px112_sc1", 7, 1, 4, 19, &rows_launch<7, 1, 4, 19, kSc1>},
+    {"direct_rows_k76_co64_px64_sc1", 4, 1, 4, 19, &rows_launch<4, 1, 4, 19, kSc1>},
+    {"direct_rows_k76_co64_px32_sc1", 2, 1, 4, 19, &rows_launch<2, 1, 4, 19, kSc1>},
+    {"direct_rows_k76_co32_px128_sc1", 4, 2, 2, 19, &rows_launch<4, 2, 2, 19, kSc1>},
+    {"direct_rows_k76_co32_px64_sc1", 2, 2, 2, 19, &rows_launch<2, 2, 2, 19, kSc1>},
+    {"direct_rows_k76_co16_px64_sc1", 1, 4, 1, 19, &rows_launch<1, 4, 1, 19, kSc1>},
+    {"direct_rows_k148_co64_px112_sc1", 7, 1, 4, 37, &rows_launch<7, 1, 4, 37, kSc1>},
+    {"direct_rows_k148_co64_px64_sc1", 4, 1, 4, 37, &rows_launch<4, 1, 4, 37, kSc1>},
+    {"direct_rows_k148_co64_px32_sc1", 2, 1, 4, 37, &rows_launch<2, 1, 4, 37, kSc1>},
+    {"direct_rows_k148_co32_px128_sc1", 4, 2, 2, 37, &rows_launch<4, 2, 2, 37, kSc1>},
+    {"direct_rows_k148_co32_px64_sc1", 2, 2, 2, 37, &rows_launch<2, 2, 2, 37, kSc1>},
+    {"direct_rows_k148_co16_px64_sc1", 1, 4, 1, 37, &rows_launch<1, 4, 1, 37, kSc1>},
 };
 constexpr int kNumRows = sizeof(kRows) / sizeof(kRows[0]);
 constexpr int kFirstRows = kFirstLowc + kNumLowc;
 constexpr int kRowsLdsFloats = 16384;  // 64 KiB
+
+// LDS words after the weight area: the biases, or as far as the slots past
+// C_in*K*K of the last channel's weights are read.
+int rows_slack(const RowsVariant &d) { return std::max(64, 4 * d.steps); }
 
 RowsArgs rows_args(const ConvShape &s, const RowsVariant &d)
 {
@@ -627,7 +652,7 @@ RowsArgs rows_args(const ConvShape &s, const RowsVariant &d)
     // The 16-byte row layout where W is a multiple of 4 and it fits in LDS.
     if (s.w % 4 == 0) {
         const int c16 = ceil_div(a.lw + 3, 256);
-        if ((int64_t)(s.c_in * s.k + 1) * 256 * c16 + a.wregion + 64 <= kRowsLdsFloats) {
+        if ((int64_t)(s.c_in * s.k + 1) * 256 * c16 + a.wregion + rows_slack(d) <= kRowsLdsFloats) {
             a.chunks16 = c16;
             a.lwp = 256 * c16;
         }
@@ -705,8 +730,37 @@ bool direct_is_lowc(int v) { return v >= kFirstLowc && v < kFirstRows + kNumRows
 
 int direct_lowc_max_kt(int v)
 {
-    if (v >= kFirstRows && v < kFirstRows + kNumRows) return 28;
+    if (v >= kFirstRows && v < kFirstRows + kNumRows) return 4 * kRows[v - kFirstRows].steps;
     return direct_is_lowc(v) ? 4 * kLowc[v - kFirstLowc].steps : 0;
+}
+
+// Modelled time (us, from a graph) of a conv_direct_rows plan: the rounds of
+// workgroups over 256 CUs, each staging its rows and weights by DMA and then
+// running its chain of 16x16x4 matrix steps.  Fitted to 116 measurements over
+// 23 first-layer shapes (relative error 10% r.m.s., 25% at most); the variant
+// it picks ran within 11% of the fastest of its family on each.
+double direct_rows_us(const ConvShape &s, const ilpm_plan &p)
+{
+    const RowsVariant &d = kRows[p.variant - kFirstRows];
+    const RowsArgs a = rows_args(s, d);
+    const int chunks = a.chunks16 > 0 ? a.chunks16 : a.chunks;
+    const int dmas = s.c_in * s.k * chunks + ceil_div(16 * d.cw * a.kt, a.w16 ? 256 : 64) + 1;
+    return 2.95 + ceil_div(p.grid, 256) * (0.101 * dmas + 0.0198 * d.steps * d.nb);
+}
+
+bool direct_best_rows(const ConvShape &s, ilpm_plan *p)
+{
+    double best = 1e30;
+    for (int v = kFirstRows; v < kFirstRows + kNumRows; ++v) {
+        ilpm_plan q;
+        if (!direct_make_plan(s, v, &q)) continue;
+        const double us = direct_rows_us(s, q);
+        if (us < best) {
+            best = us;
+            *p = q;
+        }
+    }
+    return best < 1e30;
 }
 
 bool direct_make_plan(const ConvShape &s, int variant, ilpm_plan *p)
@@ -758,14 +812,14 @@ bool direct_make_plan(const ConvShape &s, int variant, ilpm_plan *p)
         const RowsVariant &d = kRows[variant - kFirstRows];
         const int64_t kt = (int64_t)s.c_in * s.k * s.k;
         const int64_t plane = (int64_t)s.h_out * s.w_out;
-        // The whole contraction in one run of 7 matrix steps; 31-bit byte
+        // The whole contraction in one run of matrix steps; 31-bit byte
         // offsets; the input rows and the zero row within 64 KiB of LDS.
-        if (kt > 28) return false;
+        if (kt > 4 * d.steps) return false;
         if ((int64_t)s.c_in * s.h * s.w * 4 >= (1LL << 31) || (int64_t)s.c_out * kt * 4 >= (1LL << 31) ||
             (int64_t)s.c_out * plane * 4 >= (1LL << 31))
             return false;
         const RowsArgs a = rows_args(s, d);
-        const int64_t lds_floats = (int64_t)(s.c_in * s.k + 1) * a.lwp + a.wregion + 64;
+        const int64_t lds_floats = (int64_t)(s.c_in * s.k + 1) * a.lwp + a.wregion + rows_slack(d);
         if (lds_floats > kRowsLdsFloats) return false;
         const int64_t units = (int64_t)s.h_out * a.segs * a.co_groups;
         if (units > 0x7fffffffLL) return false;

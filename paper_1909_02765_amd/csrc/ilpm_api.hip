@@ -180,15 +180,27 @@ int compute_base_plan(const ConvShape &s, ilpm_plan *p, bool prepacked, bool poo
     return ILPM_ERR_UNSUPPORTED;
 }
 
-// The base plan, or for a shape that no table lists the bf16-split plan with
-// the shortest modelled time, where that is at most 0.95 times the base
-// plan's.  Against a direct (VALU) plan, which has no model, a bf16-split one
-// is taken from 16 input channels on: with fewer most of its 16-, 64- or
-// 8-channel stage is padding and the low-channel matrix-core kernels or the
-// VALU kernel's first-layer shapes are near (measured, from a graph: 1x1
-// stride 2 64->128 at 112^2 83.6 us direct, 5.7 bf16-split; 5x5 stride 2
-// 32->64 at 224^2 124 us, 20.7).  A plan that needs more than the no-alloc
-// array keeps to the base plan, so that the no-alloc call goes on taking it.
+// The base plan, or for a shape that no table lists:
+// - From 16 input channels on, the bf16-split plan with the shortest modelled
+//   time where that is at most 0.95 times the base plan's, or where the base
+//   plan is a direct (VALU) one, which has no model (measured, from a graph:
+//   1x1 stride 2 64->128 at 112^2 83.6 us direct, 5.7 bf16-split; 5x5 stride
+//   2 32->64 at 224^2 124 us, 20.7).  With fewer channels most of its stage of
+//   16, 64 or 8 channels is padding (3x3 stride 2 3->32 at 320^2: 9.7 us, the
+//   row kernel 4.6).  A plan that needs more than the no-alloc array keeps to
+//   the base plan, so that the no-alloc call goes on taking it.
+// - Else, where the base plan is direct, the row kernel if it takes the whole
+//   contraction (C_in*K*K <= 148): 7x7 stride 2 3->64 at 224^2 22.2 us direct,
+//   9.0 by rows; 7x7 1->24 at 300^2 11.5, 10.0; 5x5 stride 2 3->41 at 26^2
+//   13.9, 5.1.
+// - Else, in place of the LDS-tiled kernel for plain calls on OIHW weights, the
+//   row kernel at K >= 5 with C_in*K*K <= 76 and at a stride with C_in*K*K <=
+//   28: those tiles stage 8 channels or more (5x5 3->64 at 224^2 12.2 us, 9.2
+//   by rows; 5x5 1->52 at 175x121 6.2, 4.7; 3x3 stride 2 3->32 at 299^2 5.8,
+//   4.9).  At a stride with more channels (3x3 8->128 at 300^2 11.9, 15.6 by
+//   rows) and for 3x3 at stride 1, whose tiles stage 4 (4->64 at 320x240 9.5,
+//   11.8 by rows), the tiled kernel is ahead.  Pooled and prepacked calls keep
+//   it too: it pools in its epilogue and reads the packed layout.
 int compute_plan(const ConvShape &s, ilpm_plan *p, bool prepacked, bool pooled)
 {
     bool tuned;
@@ -196,23 +208,33 @@ int compute_plan(const ConvShape &s, ilpm_plan *p, bool prepacked, bool pooled)
     const Overrides &o = overrides();
     if (tuned || o.path >= 0 || o.splits > 0 || o.tile_h > 0) return rc;
     const bool direct = rc == ILPM_OK && p->path == ILPM_PATH_DIRECT;
-    if (direct && (direct_is_lowc(p->variant) || s.c_in < 16)) return rc;
-    double best = rc == ILPM_OK && !direct ? 0.95 * igemm_plan_us(s, *p, pooled) : 1e30;
-    for (int v = 0; v < igemm_num_variants(); ++v) {
-        bool even;
-        if (!igemm_is_split(v, &even) || (even && !pooled)) continue;
-        for (int splits : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
-            ilpm_plan q;
-            if (!igemm_make_plan(s, v, splits, &q) || q.splits != splits) continue;
-            if (igemm_workspace_bytes(q, s, 0) > ILPM_NOALLOC_SCRATCH_BYTES) continue;
-            const double us = igemm_plan_us(s, q, pooled);
-            if (us < best) {
-                best = us;
-                *p = q;
+    if (direct && direct_is_lowc(p->variant)) return rc;
+    if (s.c_in >= 16) {
+        double best = rc == ILPM_OK && !direct ? 0.95 * igemm_plan_us(s, *p, pooled) : 1e30;
+        bool found = false;
+        for (int v = 0; v < igemm_num_variants(); ++v) {
+            bool even;
+            if (!igemm_is_split(v, &even) || (even && !pooled)) continue;
+            for (int splits : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
+                ilpm_plan q;
+                if (!igemm_make_plan(s, v, splits, &q) || q.splits != splits) continue;
+                if (igemm_workspace_bytes(q, s, 0) > ILPM_NOALLOC_SCRATCH_BYTES) continue;
+                const double us = igemm_plan_us(s, q, pooled);
+                if (us < best) {
+                    best = us;
+                    *p = q;
+                    found = true;
+                }
             }
         }
+        if (found) return ILPM_OK;
     }
-    return best < 1e30 ? ILPM_OK : rc;
+    if (rc != ILPM_OK) return rc;
+    const int64_t kt = (int64_t)s.c_in * s.k * s.k;
+    ilpm_plan q;
+    const bool small = (s.k >= 5 && kt <= 76) || (s.stride > 1 && kt <= 28);
+    if ((direct || (small && !prepacked && !pooled)) && direct_best_rows(s, &q)) *p = q;
+    return rc;
 }
 
 // Plans already chosen, by shape: a direct-mapped table, so a call on a shape
