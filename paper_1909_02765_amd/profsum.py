@@ -46,7 +46,7 @@ def _bench_line(log):
 
 def is_conv_kernel(name):
     """The convolution kernels proper (not the weight packing or the split sum)."""
-    return ("conv_igemm" in name or "conv_direct" in name) and "pack_weights" not in name
+    return ("conv_igemm" in name or "conv_split<" in name or "conv_direct" in name) and "pack_weights" not in name
 
 
 def dispatch_counters(d):
