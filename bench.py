@@ -42,6 +42,9 @@ sys.path.insert(0, ROOT)
 METRIC = ("batch-1 conv2d fwd µs/layer and GFLOP/s (2·C_out·C_in·K²·H_out·W_out)"
           " + % roofline")
 PEAK_FP32_TFLOPS = 157.3   # MI355X dense fp32 (matrix cores)
+# Kernels on bf16 parts ("_b3_" variants) do six bf16 products per fp32 one:
+# their ceiling is a sixth of the dense bf16 rate (2500 TFLOP/s).
+PEAK_B3_TFLOPS = round(2500.0 / 6, 1)
 PEAK_HBM_GBS = 8000.0      # MI355X HBM3E
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 
@@ -59,8 +62,13 @@ def layer_work(c_in, h, w, c_out, k, s, p, bias):
     return flops, nbytes, ho, wo
 
 
-def roofline_floor_us(flops, nbytes):
-    tc = flops / (PEAK_FP32_TFLOPS * 1e12) * 1e6
+def plan_peak_tflops(ilpm, plan):
+    """Rate of the matrix instructions that a plan's kernel uses, in fp32 work."""
+    return PEAK_B3_TFLOPS if "_b3_" in ilpm.variant_name(plan.path, plan.variant) else PEAK_FP32_TFLOPS
+
+
+def roofline_floor_us(flops, nbytes, peak_tflops=PEAK_FP32_TFLOPS):
+    tc = flops / (peak_tflops * 1e12) * 1e6
     tm = nbytes / (PEAK_HBM_GBS * 1e9) * 1e6
     return max(tc, tm), ("mfma" if tc >= tm else "hbm")
 
@@ -420,11 +428,12 @@ def main():
     r = bench_case(torch, ilpm, case, args.steps, args.warmup, graph=True)
     us = r["us"]
     gflops = r["flops"] / (us * 1e-6) / 1e9
-    floor_us, bound = roofline_floor_us(r["flops"], r["nbytes"])
+    peak = plan_peak_tflops(ilpm, r["plan"])
+    floor_us, bound = roofline_floor_us(r["flops"], r["nbytes"], peak)
     digest = kernel_source_digest()
     if bound == "mfma":
         roof = {"bound": "mfma", "achieved": round(r["flops"] / (us * 1e-6) / 1e12, 3),
-                "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s"}
+                "peak": peak, "unit": "TFLOP/s"}
     else:
         roof = {"bound": "hbm", "achieved": round(r["nbytes"] / (us * 1e-6) / 1e9, 1),
                 "peak": PEAK_HBM_GBS, "unit": "GB/s"}
@@ -471,7 +480,7 @@ def main():
         rows = []
         for c in workloads.ALL_CASES:
             rr = bench_case(torch, ilpm, c, max(200, args.steps // 4), 1000, graph=True)
-            fl, kind = roofline_floor_us(rr["flops"], rr["nbytes"])
+            fl, kind = roofline_floor_us(rr["flops"], rr["nbytes"], plan_peak_tflops(ilpm, rr["plan"]))
             rows.append({"layer": c.name, "us": round(rr["us"], 3), "graph_us": round(rr["graph_us"], 3),
                          "prepacked_us": round(rr["prepacked_us"], 3), "cold_us": round(rr["cold_us"], 3),
                          "cold_hbm_gbs": round(rr["nbytes"] / rr["cold_us"] / 1e3, 1),
@@ -531,8 +540,8 @@ def config_rows(torch, ilpm, workloads, headline, failures, steps=500, warmup=20
         out = torch.empty((1, c.c_out, ho, wo), device="cuda", dtype=torch.float32)
         us = time_layer(torch, ilpm, xd, wd, bd, c.stride, c.pad, out, steps, warmup)
         gus = time_layer_graph(torch, ilpm, xd, wd, bd, c.stride, c.pad, out, steps)
-        fl, kind = roofline_floor_us(flops, nbytes)
         plan = ilpm.plan(c.c_in, c.h, c.w, c.c_out, c.k, c.stride, c.pad)
+        fl, kind = roofline_floor_us(flops, nbytes, plan_peak_tflops(ilpm, plan))
         row = {"workload": name, "us": round(us, 3), "graph_us": round(gus, 3),
                "gflops": round(flops / us / 1e3, 1), "bound": kind, "floor_us": round(fl, 3),
                "frac": round(fl / us, 4), "plan": ilpm.variant_name(plan.path, plan.variant) + f" x{plan.splits}"}
@@ -582,7 +591,7 @@ def bench_vgg16_layers(torch, ilpm, workloads, steps):
         out = torch.empty((1, co, hw, hw), device="cuda", dtype=torch.float32)
         us = time_layer(torch, ilpm, x, w, None, 1, 1, out, steps, 200)
         flops, nbytes, _, _ = layer_work(ci, hw, hw, co, 3, 1, 1, False)
-        fl, kind = roofline_floor_us(flops, nbytes)
+        fl, kind = roofline_floor_us(flops, nbytes, plan_peak_tflops(ilpm, ilpm.plan(ci, hw, hw, co, 3, 1, 1)))
         out_rows.append({"layer": name, "us": round(us, 3), "frac": round(fl / us, 4), "floor_us": fl,
                          "gflop": flops / 1e9, "bound": kind})
         ilpm.relu_(out)
@@ -635,8 +644,8 @@ def bench_vgg16(torch, ilpm, workloads, steps):
         us = time_layer(torch, ilpm, x, w, None, 1, 1, out, steps, 1000)
         gus = time_layer_graph(torch, ilpm, x, w, None, 1, 1, out, steps)
         flops, nbytes, _, _ = layer_work(ci, hw, hw, co, 3, 1, 1, False)
-        fl, kind = roofline_floor_us(flops, nbytes)
         plan = ilpm.plan(ci, hw, hw, co, 3, 1, 1)
+        fl, kind = roofline_floor_us(flops, nbytes, plan_peak_tflops(ilpm, plan))
         rows.append({"layer": f"vgg16_{name}", "us": round(us, 3), "graph_us": round(gus, 3),
                      "gflops": round(flops / us / 1e3, 1),
                      "floor_us": round(fl, 3), "bound": kind, "frac": round(fl / us, 4), "plan": plan.as_dict()})
