@@ -818,6 +818,8 @@ bool direct_make_plan(const ConvShape &s, int variant, ilpm_plan *p)
         if ((int64_t)s.c_in * s.h * s.w * 4 >= (1LL << 31) || (int64_t)s.c_out * kt * 4 >= (1LL << 31) ||
             (int64_t)s.c_out * plane * 4 >= (1LL << 31))
             return false;
+        // (A segment's input span first, in 64 bits: rows_args keeps it in 32.)
+        if ((16LL * d.nb * d.pw - 1) * s.stride + s.k > kRowsLdsFloats) return false;
         const RowsArgs a = rows_args(s, d);
         const int64_t lds_floats = (int64_t)(s.c_in * s.k + 1) * a.lwp + a.wregion + rows_slack(d);
         if (lds_floats > kRowsLdsFloats) return false;

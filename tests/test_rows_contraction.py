@@ -44,6 +44,30 @@ def test_default_plan(shape, rows):
         assert q.path == ilpm.PATH_IGEMM
 
 
+@pytest.mark.parametrize("log2", [12, 16, 20, 24, 26, 27, 28, 29, 30, 31])
+def test_strides_longer_than_the_lds(log2):
+    """Strides whose segments do not fit in LDS, also where their length passes
+    2^31: no row variant plans them unless its segment fits, and every plan's
+    LDS is what its rows need (host only)."""
+    for stride in {2 ** log2 - 1, min(2 ** log2, 2 ** 31 - 1), 3 * 2 ** (log2 - 2)}:
+        for c_in, h, w, k, pad in [(1, 3, 3, 3, 0), (3, 5, 5, 5, 2), (3, 224, 224, 7, 3)]:
+            for p in [ilpm.plan(c_in, h, w, 64, k, stride, pad)] + _row_plans(c_in, h, w, 64, k, stride, pad):
+                assert 0 <= p.lds_bytes <= 160 * 1024
+                if p.path == ilpm.PATH_DIRECT and "_rows_" in _name(p.variant):
+                    assert p.lds_bytes >= 4 * c_in * k * ((p.tile_w - 1) * stride + k)
+
+
+def _row_plans(*shape):
+    plans = []
+    for v in range(ilpm.num_variants(ilpm.PATH_DIRECT)):
+        if "_rows_" in _name(v):
+            try:
+                plans.append(ilpm.plan_variant(*shape, ilpm.PATH_DIRECT, v, 1))
+            except ilpm.IlpmError:
+                pass
+    return plans
+
+
 @pytest.fixture
 def gpu():
     import gpu_common
