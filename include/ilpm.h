@@ -97,9 +97,7 @@ typedef struct ilpm_plan {
  * array of tile arrival counts that the library holds; calls that overlap in
  * time on one device and both use split plans must be ordered on one stream.
  * Workspace: the one registered with ilpm_set_workspace (ILPM_ERR_WORKSPACE
- * if it is too small), else the library's own for the current device.  (Where
- * a bf16-split default plan finds no room for its partial sums, the fp32
- * variants' plan runs instead, and only what that one needs can be refused.)  A
+ * if it is too small), else the library's own for the current device.  A
  * call that needs more than the library's own holds allocates a larger one
  * (hipMalloc: no synchronisation, no free -- the smaller buffer is kept
  * until the process ends, because work already enqueued or a HIP graph
@@ -195,8 +193,11 @@ int ilpm_conv2d_validate(const void *in, const void *w, const void *bias,
  * ilpm_conv2d_plan -- the plan ilpm_conv2d_fwd uses for this shape (path,
  * tile, split count, grid, workspace): the fastest plan measured on MI355X
  * for this exact shape when the compiled-in tuning table lists it, else the
- * best by cost models fitted to measured times.  Pure host.  A shape's plan is chosen once and kept
- * (a table in the library), so later calls cost a lookup.
+ * best by cost models fitted to measured times (bf16-split plans among them
+ * only as far as they need no more than the fp32 plan of the shape: no splits
+ * where that has none, no more workspace, pooling in the kernel where that
+ * does).  Pure host.  A shape's plan is chosen once and kept (a table in the
+ * library), so later calls cost a lookup.
  * Environment overrides, read once, the first time the library plans a call
  * (for sweeps and ablations; any of them bypasses the tuning table):
  *   ILPM_FORCE_PATH=direct|igemm  only that kernel family (igemm: the

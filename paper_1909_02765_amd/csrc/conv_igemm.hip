@@ -385,6 +385,8 @@ bool igemm_is_split(int variant, bool *even)
     return true;
 }
 
+bool igemm_pools(const ilpm_plan &p) { return p.splits == 1 && variant_at(p.variant).poolable; }
+
 double igemm_plan_cost(const ConvShape &s, const ilpm_plan &p)
 {
     const Variant &d = variant_at(p.variant);

@@ -187,8 +187,12 @@ int compute_base_plan(const ConvShape &s, ilpm_plan *p, bool prepacked, bool poo
 //   1x1 stride 2 64->128 at 112^2 83.6 us direct, 5.7 bf16-split; 5x5 stride
 //   2 32->64 at 224^2 124 us, 20.7).  With fewer channels most of its stage of
 //   16, 64 or 8 channels is padding (3x3 stride 2 3->32 at 320^2: 9.7 us, the
-//   row kernel 4.6).  A plan that needs more than the no-alloc array keeps to
-//   the base plan, so that the no-alloc call goes on taking it.
+//   row kernel 4.6).  Its demands stay within the base plan's: split only
+//   where that is, with no more workspace (nor more than the no-alloc array),
+//   and pooling in the kernel where that does.  Split plans of one device
+//   must not overlap in time and cannot grow their workspace under capture,
+//   so a shape that ran unsplit, on any streams, in a graph or beside a small
+//   registered workspace, goes on doing so.
 // - Else, where the base plan is direct, the row kernel if it takes the whole
 //   contraction (C_in*K*K <= 148): 7x7 stride 2 3->64 at 224^2 22.2 us direct,
 //   9.0 by rows; 7x7 1->24 at 300^2 11.5, 10.0; 5x5 stride 2 3->41 at 26^2
@@ -209,16 +213,19 @@ int compute_plan(const ConvShape &s, ilpm_plan *p, bool prepacked, bool pooled)
     if (tuned || o.path >= 0 || o.splits > 0 || o.tile_h > 0) return rc;
     const bool direct = rc == ILPM_OK && p->path == ILPM_PATH_DIRECT;
     if (direct && direct_is_lowc(p->variant)) return rc;
-    if (s.c_in >= 16) {
-        double best = rc == ILPM_OK && !direct ? 0.95 * igemm_plan_us(s, *p, pooled) : 1e30;
+    if (s.c_in >= 16 && rc == ILPM_OK) {
+        const ilpm_plan base = *p;
+        const bool base_pools = !direct && igemm_pools(base);
+        const size_t room = direct || base.splits == 1 ? 0 : std::min(base.workspace_bytes, ILPM_NOALLOC_SCRATCH_BYTES);
+        double best = direct ? 1e30 : 0.95 * igemm_plan_us(s, base, pooled);
         bool found = false;
         for (int v = 0; v < igemm_num_variants(); ++v) {
             bool even;
-            if (!igemm_is_split(v, &even) || (even && !pooled)) continue;
+            if (!igemm_is_split(v, &even) || (even && !pooled && !base_pools) || (!even && base_pools)) continue;
             for (int splits : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
                 ilpm_plan q;
                 if (!igemm_make_plan(s, v, splits, &q) || q.splits != splits) continue;
-                if (igemm_workspace_bytes(q, s, 0) > ILPM_NOALLOC_SCRATCH_BYTES) continue;
+                if (q.workspace_bytes > room) continue;
                 const double us = igemm_plan_us(s, q, pooled);
                 if (us < best) {
                     best = us;
@@ -242,7 +249,7 @@ int compute_plan(const ConvShape &s, ilpm_plan *p, bool prepacked, bool pooled)
 // the cost-model sweep.
 struct PlanSlot {
     bool used = false;
-    int mode;  // 1: prepacked weights, 2: pooled epilogue, 4: base plan
+    int mode;  // 1: prepacked weights, 2: pooled epilogue
     ConvShape s;
     int rc;
     ilpm_plan p;
@@ -256,10 +263,9 @@ bool same_shape(const ConvShape &a, const ConvShape &b)
            a.stride == b.stride && a.pad == b.pad;
 }
 
-// base: the plan without the bf16-split variants (compute_base_plan).
-int choose_plan(const ConvShape &s, ilpm_plan *p, bool prepacked = false, bool pooled = false, bool base = false)
+int choose_plan(const ConvShape &s, ilpm_plan *p, bool prepacked = false, bool pooled = false)
 {
-    const int mode = (prepacked ? 1 : 0) | (pooled ? 2 : 0) | (base ? 4 : 0);
+    const int mode = (prepacked ? 1 : 0) | (pooled ? 2 : 0);
     uint64_t h = 1469598103934665603ull;  // FNV-1a over the seven sizes and the mode
     for (int v : {s.c_in, s.h, s.w, s.c_out, s.k, s.stride, s.pad, mode})
         h = (h ^ (uint32_t)v) * 1099511628211ull;
@@ -272,8 +278,7 @@ int choose_plan(const ConvShape &s, ilpm_plan *p, bool prepacked = false, bool p
         }
     }
     ilpm_plan q = {};
-    bool tuned;
-    const int rc = base ? compute_base_plan(s, &q, prepacked, pooled, &tuned) : compute_plan(s, &q, prepacked, pooled);
+    const int rc = compute_plan(s, &q, prepacked, pooled);
     std::lock_guard<std::mutex> lk(g_mu);
     slot.used = true;
     slot.mode = mode;
@@ -434,29 +439,6 @@ int run(const float *in, const float *w, const float *bias, const ConvShape &s, 
         e = direct_launch(p, s, in, w, bias, out, stream, relu);
     }
     return e == hipSuccess ? ILPM_OK : hip_fail(e);
-}
-
-// A call with the shape's default plan.  Where that is a bf16-split plan whose
-// partial sums find no room (a registered workspace that is too small, a
-// capture that may not allocate, the no-alloc array), the base plan runs
-// instead: what it needs decides whether the call is refused.
-int run_default(const float *in, const float *w, const float *bias, const ConvShape &s, float *out,
-                hipStream_t stream, int epilogue = 0, bool use_scratch = false)
-{
-    const bool pooled = (epilogue & ILPM_EPI_MAXPOOL2) != 0;
-    ilpm_plan p;
-    int rc = choose_plan(s, &p, false, pooled);
-    if (rc != ILPM_OK) return rc;
-    auto go = [&] {
-        if (use_scratch && workspace_need(p, s, epilogue) > ILPM_NOALLOC_SCRATCH_BYTES) return (int)ILPM_ERR_WORKSPACE;
-        return run(in, w, bias, s, out, p, stream, false, epilogue, use_scratch);
-    };
-    rc = go();
-    bool even;
-    if (rc == ILPM_ERR_WORKSPACE && p.path == ILPM_PATH_IGEMM && igemm_is_split(p.variant, &even) &&
-        choose_plan(s, &p, false, pooled, true) == ILPM_OK)
-        rc = go();
-    return rc;
 }
 
 // Bytes of the prepacked weights of plan p (0 with *rc set on a bad plan).
@@ -651,7 +633,10 @@ int ilpm_conv2d_fwd(const float *in, const float *w, const float *bias, int C_in
     if (rc != ILPM_OK) return rc;
     rc = validate(in, w, bias, s, out);
     if (rc != ILPM_OK) return rc;
-    return run_default(in, w, bias, s, out, stream);
+    ilpm_plan p;
+    rc = choose_plan(s, &p);
+    if (rc != ILPM_OK) return rc;
+    return run(in, w, bias, s, out, p, stream);
 }
 
 int ilpm_arch_supported(const char *gcn_arch_name) { return arch_status(gcn_arch_name); }
@@ -664,7 +649,11 @@ int ilpm_conv2d_fwd_noalloc(const float *in, const float *w, const float *bias, 
     if (rc != ILPM_OK) return rc;
     rc = validate(in, w, bias, s, out);
     if (rc != ILPM_OK) return rc;
-    return run_default(in, w, bias, s, out, stream, 0, true);
+    ilpm_plan p;
+    rc = choose_plan(s, &p);
+    if (rc != ILPM_OK) return rc;
+    if (workspace_need(p, s, 0) > ILPM_NOALLOC_SCRATCH_BYTES) return ILPM_ERR_WORKSPACE;
+    return run(in, w, bias, s, out, p, stream, false, 0, true);
 }
 
 int ilpm_conv2d_fwd_plan(const float *in, const float *w, const float *bias, int C_in, int H, int W, int C_out,
@@ -762,10 +751,15 @@ int ilpm_conv2d_fwd_epilogue(const float *in, const float *w, const float *bias,
     if ((epilogue & ILPM_EPI_MAXPOOL2) && (s.h_out < 2 || s.w_out < 2)) return ILPM_ERR_INVALID_ARG;
     rc = validate(in, w, bias, s, out, epilogue);
     if (rc != ILPM_OK) return rc;
-    if (!plan) return run_default(in, w, bias, s, out, stream, epilogue);
-    rc = check_plan(s, *plan);
+    ilpm_plan p;
+    if (plan) {
+        rc = check_plan(s, *plan);
+        p = *plan;
+    } else {
+        rc = choose_plan(s, &p, false, (epilogue & ILPM_EPI_MAXPOOL2) != 0);
+    }
     if (rc != ILPM_OK) return rc;
-    return run(in, w, bias, s, out, *plan, stream, false, epilogue);
+    return run(in, w, bias, s, out, p, stream, false, epilogue);
 }
 
 int ilpm_winograd_filter_size(int C_in, int C_out, size_t *bytes)

@@ -46,6 +46,8 @@ double igemm_plan_us(const ConvShape &s, const ilpm_plan &p, bool pooled);
 // Whether a variant is a bf16-split one (conv_split.h), and then whether its
 // tiles have even sides (the 2x2 max-pool stays in the kernel).
 bool igemm_is_split(int variant, bool *even);
+// Whether a plan's 2x2 max-pool epilogue stays in its kernel.
+bool igemm_pools(const ilpm_plan &p);
 // packed: w is in the variant's prepacked layout (igemm_pack) instead of OIHW.
 // epilogue: ILPM_EPI_* bits.  With ILPM_EPI_MAXPOOL2, out is the pooled
 // [C_out][H_out/2][W_out/2] tensor and the workspace holds every split's

@@ -1,6 +1,6 @@
 """The bf16-split variants (fp32 operands as three bf16 parts): what the tests
 over all variants do not reach -- 1x1 filters with a stride, tile edges, values
-that are not finite, and the workspace rules of their default plans.  Against
+that are not finite, and what their default plans may need.  Against
 the oracle with its own tolerance; the split's products are exact to 2^-24 and
 its sums rounded less often than an fp32 chain's, so no wider one is needed."""
 import numpy as np
@@ -8,7 +8,6 @@ import pytest
 
 import oracle
 import paper_1909_02765_amd as ilpm
-import workloads
 
 SPLIT = [v for v in range(ilpm.num_variants(ilpm.PATH_IGEMM)) if "_b3_" in ilpm.variant_name(ilpm.PATH_IGEMM, v)]
 
@@ -47,6 +46,44 @@ def test_default_plans_stay_within_the_noalloc_array():
             seen += 1
             assert p.workspace_bytes <= ilpm.NOALLOC_SCRATCH_BYTES
     assert seen >= 3
+
+
+# Shapes, and the workspace that the fp32 variants' plan of each needs.
+BASE_WORKSPACE = [
+    ((640, 20, 20, 640, 3, 1, 1), 0), ((388, 15, 16, 399, 3, 1, 1), 0), ((256, 115, 106, 32, 3, 1, 1), 0),
+    ((400, 56, 90, 256, 3, 1, 1), 0), ((130, 78, 78, 182, 3, 1, 1), 0), ((208, 21, 23, 224, 1, 2, 0), 0),
+    ((448, 33, 40, 112, 1, 2, 0), 0), ((240, 11, 11, 32, 1, 2, 0), 0), ((576, 89, 89, 176, 3, 2, 1), 0),
+    ((329, 47, 47, 391, 3, 2, 1), 0), ((144, 61, 68, 32, 5, 1, 2), 0), ((592, 70, 91, 32, 5, 1, 2), 0),
+    ((44, 84, 84, 52, 5, 2, 2), 0), ((30, 38, 38, 16, 5, 2, 2), 0), ((340, 53, 53, 341, 3, 1, 1), 7662952),
+    ((377, 11, 11, 579, 3, 1, 1), 3362832), ((144, 43, 43, 624, 3, 2, 1), 2416128),
+    ((606, 22, 22, 111, 5, 1, 2), 429792), ((247, 37, 56, 45, 5, 1, 2), 1491840)]
+
+
+@pytest.mark.parametrize("shape,most", BASE_WORKSPACE, ids=str)
+def test_default_plans_need_no_more_than_the_fp32_plans(shape, most):
+    """What a caller may do with a shape (overlap calls of it on several
+    streams, capture the first call, register a small workspace) does not
+    shrink with the bf16-split plans: unsplit where the fp32 plan is, on both
+    weight layouts and with either epilogue, and never more workspace."""
+    for prepacked in (False, True):
+        for epi in (0, ilpm.EPI_RELU | ilpm.EPI_MAXPOOL2):
+            p = ilpm.plan_for(*shape, epi, prepacked)
+            assert p.workspace_bytes <= most
+            assert most > 0 or p.splits == 1
+
+
+@pytest.mark.parametrize("shape", [(512, 105, 105, 368, 1, 1, 0), (320, 98, 145, 128, 3, 1, 1),
+                                   (46, 171, 171, 51, 3, 1, 1), (79, 113, 113, 493, 3, 1, 1), (17, 45, 45, 72, 5, 1, 2)],
+                         ids=str)
+def test_plain_plans_pool_where_the_fp32_plans_do(shape):
+    """Shapes whose fp32 plan pools in its kernel when the pooled epilogue is
+    called with the plain plan: the default plain plan does too."""
+    for prepacked in (False, True):
+        p = ilpm.plan_for(*shape, 0, prepacked)
+        assert p.path == ilpm.PATH_IGEMM and p.splits == 1
+        assert p.tile_h % 2 == 0 and p.tile_w % 2 == 0
+        if p.variant in SPLIT:
+            assert _name(p.variant).endswith("_even")
 
 
 @pytest.fixture
@@ -120,28 +157,42 @@ def test_values_that_are_not_finite(gpu, v):
 
 
 @pytest.mark.gpu
-def test_default_call_without_room_for_partial_sums(gpu):
-    """640->640 at 20x20: the default plan splits the channels, the plan of the
-    fp32 variants needs no workspace.  With a registered workspace that is too
-    small, and under capture with none, the call still runs."""
+@pytest.mark.parametrize("shape", [(388, 15, 16, 399, 3, 1, 1), (208, 21, 23, 224, 1, 2, 0), (144, 61, 68, 32, 5, 1, 2),
+                                   (44, 84, 84, 52, 5, 2, 2)], ids=str)
+def test_unsplit_shapes_need_no_workspace(gpu, shape):
+    """Shapes whose fp32 plan is unsplit: their default calls run beside a
+    registered workspace that is too small for any partial sums, and under
+    capture there, OIHW and packed, with the bits of the no-alloc call."""
     import torch
-    shape = (640, 20, 20, 640, 3, 1, 1)
-    p = ilpm.plan(*shape)
-    assert p.variant in SPLIT and p.splits > 1
-    x = workloads.uniform(9500, (1, 640, 20, 20), 0.0, 1.0)
-    wt = workloads.normal(9501, (640, 640, 3, 3), 0.0, workloads.he_std(640, 3))
-    ref, sab = oracle.conv2d_f64(x, wt, None, 1, 1)
-    small = torch.empty(1024, dtype=torch.float32, device="cuda")
+    c_in, h, w, c_out, k, s, pad = shape
+    x, wt, b = gpu.random_case(9500, c_in, h, w, c_out, k)
+    ref, sab = oracle.conv2d_f64(x, wt, b, s, pad)
+    xd, wd, bd = gpu.dev(x), gpu.dev(wt), gpu.dev(b)
+    plan = ilpm.plan_prepacked(*shape)
+    packed = ilpm.prepack_weights(wd, plan)
+    ho, wo = ilpm.out_size(h, k, s, pad), ilpm.out_size(w, k, s, pad)
+    out, out_packed = (torch.empty((1, c_out, ho, wo), device="cuda") for _ in range(2))
+    want = ilpm.conv2d_noalloc(xd, wd, bd, s, pad, out=out).cpu().numpy()
+    gpu.assert_matches(want, ref, sab, c_in, k, f"noalloc {shape}")
+    small = torch.empty(64, dtype=torch.float32, device="cuda")
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    torch.cuda.synchronize()
     ilpm.set_workspace(small)
     try:
-        gpu.note("[split] default call with a small registered workspace")
-        got = gpu.run_conv(x, wt, None, 1, 1)
-        gpu.assert_matches(got, ref, sab, 640, 3, "small workspace")
+        gpu.note(f"[split] {shape} with a small registered workspace")
+        np.testing.assert_array_equal(gpu.run_conv(x, wt, b, s, pad), want)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            ilpm.conv2d(xd, wd, bd, s, pad, out=out)
+            ilpm.conv2d_prepacked(xd, packed, c_out, k, bd, s, pad, out=out_packed, plan=plan)
+        for i in range(3):
+            out.fill_(float("nan"))
+            out_packed.fill_(float("nan"))
+            g.replay()
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(out.cpu().numpy(), want, err_msg=f"replay {i}")
+            np.testing.assert_array_equal(out_packed.cpu().numpy(), want, err_msg=f"replay {i}, packed")
     finally:
         torch.cuda.synchronize()
         ilpm.set_workspace(None)
-    xd, wd = gpu.dev(x), gpu.dev(wt)
-    out = torch.empty((1, 640, 20, 20), device="cuda")
-    ilpm.conv2d_noalloc(xd, wd, None, 1, 1, out=out)
-    torch.cuda.synchronize()
-    gpu.assert_matches(out.cpu().numpy(), ref, sab, 640, 3, "noalloc")
