@@ -126,7 +126,7 @@ struct Variant {
     bool even = false;     // tiles with even sides: a 2x2 max-pool stays in the kernel
     // Measured times, us, of igemm_plan_us (see there).
     struct Times {
-        double base, stage1, stage2, round, out, part, split;
+        double base, stage1, stage2, round, out, part, split, flow, piece, out_piece;
     };
     int per_cu = 1;  // workgroups a compute unit holds
     Times us = {};

@@ -4,6 +4,7 @@
 // description are in conv_igemm.h.
 #include <algorithm>
 #include <atomic>
+#include <cstring>
 #include <vector>
 
 #include "conv_igemm.h"
@@ -213,50 +214,109 @@ constexpr int kCUs = 256;
 // pixels they use).
 int halo_extent(int n, int k, int s) { return k == 1 ? n : (n - 1) * s + k; }
 
-// The tile of a bf16-split plan: of the tiles of at most px output and xpix
-// halo pixels, one with the fewest tiles over the output (every tile costs the
-// same, full or not), rows of 16 pixels (whole 64-byte stores) worth a tenth
-// more tiles (64->64 at 224^2: 15x14-pixel tiles took 6 us more to store the
-// output than 16x16-pixel ones); then the smallest halo.
-bool split_tile(const ConvShape &s, const Variant &d, int *th_out, int *tw_out)
+// Rounds of a bf16-split grid on the chip: a compute unit runs its workgroups
+// `per_cu` at a time.
+struct Rounds {
+    int pairs, singles;
+};
+Rounds split_rounds(const Variant &d, int64_t grid)
 {
+    const int per = (int)((grid + kCUs - 1) / kCUs);
+    const int pairs = d.per_cu == 2 ? per / 2 : 0;
+    return {pairs, per - 2 * pairs};
+}
+
+// 64-byte pieces of memory under the rows of a bf16-split tile, per input and
+// per output channel: n values of a row starting anywhere lie in
+// (4n + 60) / 64 of them on average, whole pieces where every row starts on
+// one.
+struct TilePieces {
+    double in, out;
+};
+TilePieces split_pieces(const ConvShape &s, int th, int tw)
+{
+    const bool whole = tw % 16 == 0 && s.w_out % 16 == 0;
+    const int hc = halo_extent(tw, s.k, s.stride), hr = halo_extent(th, s.k, s.stride);
+    TilePieces t;
+    t.out = th * (whole ? tw / 16 : (4 * tw + 60) / 64.0);
+    if (s.k == 1 && s.stride == 1 && s.pad == 0) t.in = t.out;
+    else if (s.k == 1) t.in = hr * std::min(1.0 * hc, (4.0 * hc * s.stride + 60) / 64.0);
+    else t.in = hr * (4 * hc + 60) / 64.0;
+    return t;
+}
+
+// Time of the workgroups of a bf16-split plan, us: its rounds, each a fixed
+// time and a chain of stages; a stage of two workgroups together takes stage2,
+// of one alone stage1, a little more (flow) per workgroup in all, and the
+// pieces of memory under its halo and its output their time.
+double split_work_us(const Variant &d, int64_t grid, int stages, const TilePieces &t)
+{
+    const Rounds r = split_rounds(d, grid);
+    const double pieces = stages * d.us.piece * d.cc * t.in + d.us.out_piece * d.cot * t.out;
+    return (r.pairs + r.singles) * d.us.round +
+           stages * (r.pairs * d.us.stage2 + r.singles * d.us.stage1 + grid / (double)kCUs * d.us.flow) +
+           (2 * r.pairs + r.singles) * pieces;
+}
+
+// The tile of a bf16-split plan with `splits` splits: of the tiles of at most
+// px output and xpix halo pixels, the one with the shortest modelled time --
+// the rounds that its grid takes, its workgroups in all, and the 64-byte
+// pieces under its rows.
+// Neighbouring lanes load and store neighbouring pixels of a row, so a tile of
+// short rows touches a piece per row and channel for a few floats each
+// (1x1 256->128 at 56^2, 56 pixels a tile: 22.4 us as 56x1, 8.1 as 8x8, 7.5 as
+// 1x56; 64->64 at 224^2: 28.1 as 32x8, 26.1 as 16x16, 24.5 as 8x32).
+bool split_tile(const ConvShape &s, const Variant &d, int splits, int *th_out, int *tw_out)
+{
+    const int groups = ceil_div(s.c_out, d.cot), stages = ceil_div(ceil_div(s.c_in, d.cc), splits);
     struct Memo {
         const Variant *d = nullptr;
-        int ho, wo, th, tw;
+        int ho, wo, pad, stride, groups, splits, stages, th, tw;
     };
     thread_local Memo memo[64];
-    Memo &e = memo[((unsigned)s.h_out * 31u + (unsigned)s.w_out * 7u + (unsigned)((uintptr_t)&d / sizeof(Variant))) % 64];
-    if (e.d == &d && e.ho == s.h_out && e.wo == s.w_out) {
+    unsigned hash = (unsigned)((uintptr_t)&d / sizeof(Variant));
+    for (int v : {s.h_out, s.w_out, groups, splits, stages}) hash = (hash ^ (unsigned)v) * 16777619u;
+    Memo &e = memo[(hash >> 16) % 64];
+    if (e.d == &d && e.ho == s.h_out && e.wo == s.w_out && e.pad == s.pad && e.stride == s.stride &&
+        e.groups == groups && e.splits == splits && e.stages == stages) {
         *th_out = e.th;
         *tw_out = e.tw;
         return e.th > 0;
     }
     const int step = d.even ? 2 : 1;
-    int best_th = 0, best_tw = 0;
-    int64_t best = 0;
-    for (int tw = step; tw <= d.px && tw < s.w_out + step; tw += step) {
+    int best_th = 0, best_tw = 0, best_halo = 0;
+    double best = 0;
+    auto consider = [&](int tw) {
+        if (tw > d.px) return;
         const int hc = halo_extent(tw, s.k, s.stride);
         int th = std::min(d.px / tw, s.h_out + step - 1);
         while (th > 0 && halo_extent(th, s.k, s.stride) * hc > d.xpix) --th;
         th = th / step * step;
-        if (th <= 0) continue;
+        if (th <= 0) return;
         // The same number of tiles with sides as equal as can be.
         const int nh = ceil_div(s.h_out, th), nw = ceil_div(s.w_out, tw);
         th = ceil_div(ceil_div(s.h_out, nh), step) * step;
-        if (ceil_div(ceil_div(s.w_out, nw), step) * step != tw) continue;  // a narrower tile does the same
-        const int64_t cost = (int64_t)nh * nw * (tw % 16 == 0 ? 10 : 11) * 65536 +
-                             halo_extent(th, s.k, s.stride) * hc;
-        if (best_th == 0 || cost < best) {
-            best = cost;
+        const int64_t grid = (int64_t)nh * nw * groups * splits;
+        const double us = split_work_us(d, grid, stages, split_pieces(s, th, tw));
+        const int halo = halo_extent(th, s.k, s.stride) * hc;
+        if (best_th == 0 || us < best || (us == best && halo < best_halo)) {
+            best = us;
+            best_halo = halo;
             best_th = th;
             best_tw = tw;
         }
+    };
+    // Every number of tiles across, at its narrowest tile, and rows of whole
+    // pieces.
+    const int widest = std::min(d.px, ceil_div(s.w_out, step) * step);
+    for (int tw = widest; tw > 0;) {
+        const int nw = ceil_div(s.w_out, tw);
+        const int narrow = ceil_div(ceil_div(s.w_out, nw), step) * step;
+        consider(narrow);
+        tw = narrow - step;
     }
-    e.d = &d;
-    e.ho = s.h_out;
-    e.wo = s.w_out;
-    e.th = best_th;
-    e.tw = best_tw;
+    for (int tw = 16; tw <= widest; tw += 16) consider(tw);
+    e = {&d, s.h_out, s.w_out, s.pad, s.stride, groups, splits, stages, best_th, best_tw};
     *th_out = best_th;
     *tw_out = best_tw;
     return best_th > 0;
@@ -312,9 +372,10 @@ bool igemm_make_plan(const ConvShape &s, int variant, int splits, ilpm_plan *p)
     // A stage's channels (up to CC, past C_in too) stay within 31-bit offsets.
     if ((int64_t)(s.c_in > d.cc ? s.c_in : d.cc) * s.h * s.w * 4 >= (1LL << 31)) return false;
     int th = d.th, tw = d.tw;
-    if (d.launch3 && !split_tile(s, d, &th, &tw)) return false;
-    const long tiles = (long)ceil_div(s.h_out, th) * ceil_div(s.w_out, tw) * ceil_div(s.c_out, d.cot);
-    if (tiles > 0x7fffffffL) return false;
+    // (With the number of splits to be chosen, first the tile of an unsplit plan.)
+    if (d.launch3 && !split_tile(s, d, 1, &th, &tw)) return false;
+    auto tiles_of = [&] { return (long)ceil_div(s.h_out, th) * ceil_div(s.w_out, tw) * ceil_div(s.c_out, d.cot); };
+    long tiles = tiles_of();
     const int nchunks = ceil_div(s.c_in, d.cc);
     if (splits <= 0) {
         // Enough workgroups to give every compute unit one.
@@ -330,6 +391,11 @@ bool igemm_make_plan(const ConvShape &s, int variant, int splits, ilpm_plan *p)
     if (splits > nchunks) return false;
     const int cps = ceil_div(nchunks, splits);
     splits = ceil_div(nchunks, cps);  // no empty split
+    if (d.launch3 && splits > 1) {
+        split_tile(s, d, splits, &th, &tw);
+        tiles = tiles_of();
+    }
+    if (tiles > 0x7fffffffL) return false;
     // A progressive first stage is followed by at least one more.
     if (d.pf && (cps < 2 || nchunks - (splits - 1) * cps < 2)) return false;
     if (splits > 65535) return false;
@@ -353,26 +419,55 @@ bool igemm_make_plan(const ConvShape &s, int variant, int splits, ilpm_plan *p)
     return true;
 }
 
-// Time of the second pass of a split or pooled plan by the same fits: a launch
-// and the partial sums out and in again.
-double igemm_plan_us(const ConvShape &s, const ilpm_plan &p, bool pooled)
+// Measured times of an fp32 variant, us, on OIHW and on packed weights:
+// fp32_plan_us's terms.
+struct Fp32Times {
+    const char *name;
+    struct {
+        double base, round, stage, stage_pair, stage_flow, out, split;
+    } us[2];
+};
+const Fp32Times kFp32Times[] = {
+#include "fp32_times.inc"
+};
+
+// Time of an fp32 plan, us; 0 for a variant without measured times.  Rounds of
+// 256 workgroups and their stages; how many workgroups a compute unit holds,
+// and with it the weight of a half-full round, is the variant's, so stages
+// count by whole rounds, by rounds of two workgroups and by workgroups.
+double fp32_plan_us(const ConvShape &s, const ilpm_plan &p, bool prepacked)
+{
+    static const std::vector<const Fp32Times *> times = [] {
+        std::vector<const Fp32Times *> t(num_variants(), nullptr);
+        for (int v = 0; v < num_variants(); ++v)
+            for (const Fp32Times &f : kFp32Times)
+                if (std::strcmp(f.name, variant_at(v).name) == 0) t[v] = &f;
+        return t;
+    }();
+    if (!times[p.variant]) return 0;
+    const auto &us = times[p.variant]->us[prepacked ? 1 : 0];
+    const Variant &d = variant_at(p.variant);
+    const int stages = ceil_div(ceil_div(s.c_in, d.cc), p.splits);
+    const double flow = p.grid / (double)kCUs, round = std::ceil(flow), pair = std::ceil(flow / 2);
+    const double out_mb = 4e-6 * s.c_out * s.h_out * s.w_out;
+    return us.base + round * us.round + stages * (round * us.stage + pair * us.stage_pair + flow * us.stage_flow) +
+           (p.splits > 1 ? us.split + us.out * out_mb * (2 * p.splits + 1) : us.out * out_mb);
+}
+
+// A plan's time by its variant's measured times.  A bf16-split plan's: its
+// workgroups, then the output, or with splits or a pooling pass the partial
+// sums out and in again and the second launch.
+double igemm_plan_us(const ConvShape &s, const ilpm_plan &p, bool prepacked, bool pooled)
 {
     const Variant &d = variant_at(p.variant);
     const double out_mb = 4e-6 * s.c_out * s.h_out * s.w_out;
-    const bool second = p.splits > 1 || (pooled && !(d.poolable && p.splits == 1));
+    const bool second = p.splits > 1 || (pooled && !igemm_pools(p));
     if (!d.launch3) {
-        // The cycle model, at 2.4 GHz: within 20% of the measured time on
-        // these layers but for 1x1 filters, where it was 0-40% short.
-        double us = igemm_plan_cost(s, p) / 2400.0 * (s.k == 1 ? 1.2 : 1.0);
-        if (pooled && second && p.splits == 1) us += 1.7 + 0.2 * out_mb * 2.0;
-        return us;
+        const double us = fp32_plan_us(s, p, prepacked);
+        return us > 0 && pooled && second && p.splits == 1 ? us + 1.7 + 0.4 * out_mb : us;
     }
-    // A compute unit runs its workgroups `per_cu` at a time; a stage of two
-    // together takes stage2, of one alone stage1.
     const int stages = ceil_div(ceil_div(s.c_in, d.cc), p.splits);
-    const int per = ceil_div(p.grid, kCUs);
-    const int pairs = d.per_cu == 2 ? per / 2 : 0, singles = per - 2 * pairs;
-    double us = d.us.base + (pairs + singles) * d.us.round + stages * (pairs * d.us.stage2 + singles * d.us.stage1);
+    double us = d.us.base + split_work_us(d, p.grid, stages, split_pieces(s, p.tile_h, p.tile_w));
     if (second) us += d.us.split + d.us.part * out_mb * (2 * p.splits + 1);
     else us += d.us.out * out_mb * (pooled ? 0.25 : 1.0);
     return us;

@@ -1,7 +1,8 @@
 // bf16-split kernel variants, part 0: 3x3 filters (the template is in
 // conv_split.h; the parts compile in parallel).  The times are least-squares
-// fits of igemm_plan_us's model to graph-replayed calls of some 50 layers
-// (16-1024 channels, 7^2-300x400 pixels) at 1-32 splits on one MI355X.
+// fits of igemm_plan_us's model to graph-replayed calls of 5,000 random layers
+// (16-640 channels, 7^2 to 320^2 pixels) and sweeps of tile shapes on one
+// MI355X; modelled over measured, 5th to 95th percentile: 0.87-1.09.
 #include "conv_split.h"
 
 namespace ilpm {
@@ -20,11 +21,11 @@ int variants_split0(const Variant **table)
     // per workgroup and not once per pixel half, and 32-channel stages halve
     // the barriers (16-channel stages, two waves over the pixels: 30.4 us).
     using P128L = SplitCfg<3, 1, 32, 1, 4, 1, 1, 8, 192>;
-    //                       base  stage1 stage2 round  out    part   split
-    constexpr Variant::Times tP256 = {2.43, 3.87, 0, 3.36, 0.33, 0.25, 1.6};
-    constexpr Variant::Times tP128 = {0.76, 2.31, 0, 4.59, 0.15, 0.20, 1.7};
-    constexpr Variant::Times tP64 = {2.65, 1.12, 1.69, 1.71, 0.26, 0.22, 1.7};
-    constexpr Variant::Times tP128L = {2.21, 2.42, 0, 4.90, 0.36, 0.30, 0.9};
+    //                       base  stage1 stage2 round out  part  split flow  piece out_piece
+    constexpr Variant::Times tP256 = {1.56, 3.57, 0, 1.61, 0.19, 0.16, 2.04, 1.02, 0.00018, 0.00152};
+    constexpr Variant::Times tP128 = {1.12, 2.01, 0, 3.05, 0.16, 0.19, 1.56, 0.40, 0.00062, 0.00107};
+    constexpr Variant::Times tP64 = {2.38, 1.11, 1.58, 1.49, 0.20, 0.15, 1.78, 0.06, 0.00003, 0.00155};
+    constexpr Variant::Times tP128L = {1.33, 2.00, 0, 4.19, 0.09, 0.10, 2.09, 0.46, 0.0007, 0.0013};
     static const Variant t[] = {
         make_split_variant<P256>("k3s1_b3_px256_co64", 16, 16, false, tP256),
         make_split_variant<P256>("k3s1_b3_px256_co64_even", 16, 16, true, tP256),

@@ -1,7 +1,8 @@
 // bf16-split kernel variants, part 1: 1x1 filters (the template is in
 // conv_split.h; the parts compile in parallel).  The times are least-squares
-// fits of igemm_plan_us's model to graph-replayed calls of some 50 layers
-// (16-1024 channels, 7^2-300x400 pixels) at 1-32 splits on one MI355X.
+// fits of igemm_plan_us's model to graph-replayed calls of 5,000 random layers
+// (16-640 channels, 7^2 to 320^2 pixels) and sweeps of tile shapes on one
+// MI355X; modelled over measured, 5th to 95th percentile: 0.87-1.09.
 #include "conv_split.h"
 
 namespace ilpm {
@@ -13,10 +14,10 @@ int variants_split1(const Variant **table)
     using P128 = SplitCfg<1, 1, 64, 1, 2, 2, 2, 2, 128>;
     using P64W = SplitCfg<1, 1, 64, 1, 1, 2, 2, 2, 64>;
     using P64 = SplitCfg<1, 1, 64, 1, 2, 1, 1, 4, 64>;
-    //                       base  stage1 stage2 round  out    part   split
-    constexpr Variant::Times tP128 = {6.20, 1.61, 0, 0, 0.34, 0.55, 0.1};
-    constexpr Variant::Times tP64W = {1.75, 1.30, 0, 2.12, 0.20, 0.55, 0.7};
-    constexpr Variant::Times tP64 = {3.15, 1.12, 3.44, 0.93, 0, 0.16, 1.4};
+    //                       base  stage1 stage2 round out  part  split flow  piece out_piece
+    constexpr Variant::Times tP128 = {1.69, 1.03, 0, 2.48, 0.06, 0.09, 1.85, 0.47, 0.00037, 0.00182};
+    constexpr Variant::Times tP64W = {1.51, 0.89, 0, 1.86, 0.15, 0.17, 1.79, 0.19, 0.00046, 0.00091};
+    constexpr Variant::Times tP64 = {2.08, 0.67, 0.84, 1.73, 0.19, 0.15, 1.80, 0.10, 0.00044, 0.00107};
     static const Variant t[] = {
         make_split_variant<P128>("k1s1_b3_px128_co64", 8, 16, false, tP128),
         make_split_variant<P128>("k1s1_b3_px128_co64_even", 8, 16, true, tP128),

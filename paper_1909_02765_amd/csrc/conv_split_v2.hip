@@ -1,7 +1,8 @@
 // bf16-split kernel variants, part 2: 5x5 filters and stride 2 (the template is in
 // conv_split.h; the parts compile in parallel).  The times are least-squares
-// fits of igemm_plan_us's model to graph-replayed calls of some 50 layers
-// (16-1024 channels, 7^2-300x400 pixels) at 1-32 splits on one MI355X.
+// fits of igemm_plan_us's model to graph-replayed calls of 5,000 random layers
+// (16-640 channels, 7^2 to 320^2 pixels) and sweeps of tile shapes on one
+// MI355X; modelled over measured, 5th to 95th percentile: 0.87-1.09.
 #include "conv_split.h"
 
 namespace ilpm {
@@ -15,12 +16,12 @@ int variants_split2(const Variant **table)
     using P128S2 = SplitCfg<3, 2, 16, 1, 2, 1, 2, 2, 568>;
     using P64S2 = SplitCfg<3, 2, 16, 1, 2, 1, 1, 8, 304>;
     using P64K5S2 = SplitCfg<5, 2, 8, 1, 2, 1, 1, 4, 368>;
-    //                       base  stage1 stage2 round  out    part   split
-    constexpr Variant::Times tP128K5 = {0.91, 2.22, 3.75, 2.74, 0.36, 0.17, 2.4};
-    constexpr Variant::Times tP64K5 = {1.66, 1.46, 2.15, 1.92, 0.49, 0.24, 2.3};
-    constexpr Variant::Times tP128S2 = {0, 2.50, 0, 5.74, 0, 0.09, 2.1};
-    constexpr Variant::Times tP64S2 = {1.65, 1.64, 0, 3.20, 0, 0.15, 1.7};
-    constexpr Variant::Times tP64K5S2 = {2.24, 1.49, 0, 2.85, 0.26, 0.21, 1.6};
+    //                       base  stage1 stage2 round out  part  split flow  piece out_piece
+    constexpr Variant::Times tP128K5 = {2.68, 2.04, 3.37, 1.78, 0.25, 0.17, 1.74, 0.15, 0.00051, 0};
+    constexpr Variant::Times tP64K5 = {3.13, 1.39, 2.08, 1.20, 0.42, 0.13, 1.68, 0.07, 0.0002, 0.00051};
+    constexpr Variant::Times tP128S2 = {1.52, 2.07, 0, 3.43, 0.03, 0.11, 1.91, 0.10, 0.00022, 0.00259};
+    constexpr Variant::Times tP64S2 = {1.53, 1.22, 0, 2.51, 0.02, 0.11, 1.88, 0.18, 0.0006, 0.0015};
+    constexpr Variant::Times tP64K5S2 = {0, 1.48, 0, 4.67, 0, 0.22, 1.09, 0.07, 0.00028, 0.00043};
     static const Variant t[] = {
         make_split_variant<P128K5>("k5s1_b3_px128_co32", 8, 16, false, tP128K5),
         make_split_variant<P128K5>("k5s1_b3_px128_co32_even", 8, 16, true, tP128K5),

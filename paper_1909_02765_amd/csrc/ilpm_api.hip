@@ -182,8 +182,11 @@ int compute_base_plan(const ConvShape &s, ilpm_plan *p, bool prepacked, bool poo
 
 // The base plan, or for a shape that no table lists:
 // - From 16 input channels on, the bf16-split plan with the shortest modelled
-//   time where that is at most 0.95 times the base plan's, or where the base
-//   plan is a direct (VALU) one, which has no model (measured, from a graph:
+//   time where that is at most 0.9 times the base plan's (of 2,800 random calls,
+//   700 of each weight layout and epilogue, two were then more than 2% slower
+//   than on their base plan, by 3% and 6%; at 0.95 some five times as many; a
+//   base plan whose variant has no measured times stays), or where the base
+//   plan is a direct (VALU) one (measured, from a graph:
 //   1x1 stride 2 64->128 at 112^2 83.6 us direct, 5.7 bf16-split; 5x5 stride
 //   2 32->64 at 224^2 124 us, 20.7).  With fewer channels most of its stage of
 //   16, 64 or 8 channels is padding (3x3 stride 2 3->32 at 320^2: 9.7 us, the
@@ -217,7 +220,7 @@ int compute_plan(const ConvShape &s, ilpm_plan *p, bool prepacked, bool pooled)
         const ilpm_plan base = *p;
         const bool base_pools = !direct && igemm_pools(base);
         const size_t room = direct || base.splits == 1 ? 0 : std::min(base.workspace_bytes, ILPM_NOALLOC_SCRATCH_BYTES);
-        double best = direct ? 1e30 : 0.95 * igemm_plan_us(s, base, pooled);
+        double best = direct ? 1e30 : 0.9 * igemm_plan_us(s, base, prepacked, pooled);
         bool found = false;
         for (int v = 0; v < igemm_num_variants(); ++v) {
             bool even;
@@ -226,7 +229,7 @@ int compute_plan(const ConvShape &s, ilpm_plan *p, bool prepacked, bool pooled)
                 ilpm_plan q;
                 if (!igemm_make_plan(s, v, splits, &q) || q.splits != splits) continue;
                 if (q.workspace_bytes > room) continue;
-                const double us = igemm_plan_us(s, q, pooled);
+                const double us = igemm_plan_us(s, q, prepacked, pooled);
                 if (us < best) {
                     best = us;
                     *p = q;

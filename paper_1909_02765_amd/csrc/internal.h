@@ -41,8 +41,9 @@ bool igemm_make_plan(const ConvShape &s, int variant, int splits, ilpm_plan *p);
 // rank variants; lower is better.
 double igemm_plan_cost(const ConvShape &s, const ilpm_plan &p);
 // Modelled time of a plan in us, comparable between the fp32 and the
-// bf16-split variants (pooled: with the ReLU + 2x2 max-pool epilogue).
-double igemm_plan_us(const ConvShape &s, const ilpm_plan &p, bool pooled);
+// bf16-split variants (prepacked: on packed weights; pooled: with the ReLU +
+// 2x2 max-pool epilogue); 0 for a variant without measured times.
+double igemm_plan_us(const ConvShape &s, const ilpm_plan &p, bool prepacked, bool pooled);
 // Whether a variant is a bf16-split one (conv_split.h), and then whether its
 // tiles have even sides (the 2x2 max-pool stays in the kernel).
 bool igemm_is_split(int variant, bool *even);

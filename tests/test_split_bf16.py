@@ -86,6 +86,35 @@ def test_plain_plans_pool_where_the_fp32_plans_do(shape):
             assert _name(p.variant).endswith("_even")
 
 
+@pytest.mark.parametrize("shape", [(512, 60, 60, 256, 1, 1, 0), (256, 56, 56, 128, 1, 1, 0), (256, 28, 28, 512, 1, 1, 0),
+                                   (189, 122, 164, 222, 1, 1, 0), (19, 114, 114, 196, 1, 1, 0),
+                                   (64, 224, 224, 64, 3, 1, 1)], ids=str)
+def test_tiles_are_wide(shape):
+    """Tiles of long rows: neighbouring lanes load and store neighbouring
+    pixels, and a tile of short rows touches a 64-byte piece per row and
+    channel for a few floats each (512->256 at 60^2: 47 us as 60x1 pixels, 13 as
+    1x60)."""
+    for prepacked in (False, True):
+        for epi in (0, ilpm.EPI_RELU | ilpm.EPI_MAXPOOL2):
+            p = ilpm.plan_for(*shape, epi, prepacked)
+            assert p.variant in SPLIT
+            assert p.tile_w >= min(28, p.w_out) and p.tile_w >= 4 * p.tile_h
+
+
+# Layers on which the fp32 plan was measured faster than a bf16-split one that a
+# cost model without the tiles' shape had chosen (us: fp32, bf16-split).
+FP32_FASTER = [((304, 120, 120, 304, 1, 1, 0), 36.4, 180.5), ((64, 121, 97, 128, 1, 1, 0), 7.1, 29.9),
+               ((24, 204, 204, 41, 1, 1, 0), 6.8, 12.8), ((48, 139, 139, 112, 1, 1, 0), 8.3, 14.4),
+               ((28, 84, 84, 99, 1, 1, 0), 4.7, 8.8), ((128, 193, 309, 384, 1, 1, 0), 73.7, 96.9),
+               ((18, 101, 73, 28, 5, 1, 2), 7.8, 10.2), ((23, 180, 305, 37, 3, 2, 1), 9.4, 12.1)]
+
+
+@pytest.mark.parametrize("shape,fp32,split", FP32_FASTER, ids=str)
+def test_fp32_plans_stay_where_they_are_faster(shape, fp32, split):
+    p = ilpm.plan(*shape)
+    assert p.path == ilpm.PATH_IGEMM and p.variant not in SPLIT
+
+
 @pytest.fixture
 def gpu():
     import gpu_common
