@@ -734,21 +734,47 @@ int direct_lowc_max_kt(int v)
     return direct_is_lowc(v) ? 4 * kLowc[v - kFirstLowc].steps : 0;
 }
 
-// Modelled time (us, from a graph) of a conv_direct_rows plan: the rounds of
-// workgroups over 256 CUs, each staging its rows and weights by DMA and then
-// running its chain of 16x16x4 matrix steps.  Fitted to 116 measurements over
-// 23 first-layer shapes (relative error 10% r.m.s., 25% at most); the variant
-// it picks ran within 11% of the fastest of its family on each.
+// Rounds of workgroups over 256 CUs of 160 KiB LDS: one each, and as many as
+// the LDS holds (eight at most).
+struct DirectRounds {
+    double one, full;
+};
+DirectRounds direct_rounds(const ilpm_plan &p)
+{
+    const int held = std::min(8, std::max(1, 160 * 1024 / std::max(1, p.lds_bytes)));
+    return {(double)ceil_div(p.grid, 256), (double)ceil_div(ceil_div(p.grid, 256), held)};
+}
+
+// Modelled time (us, from a graph) of a conv_direct_rows plan: workgroups that
+// each stage their rows and weights by DMA and then run their chain of 16x16x4
+// matrix steps, several at a time where the LDS holds them.  Fitted to 8,425
+// measurements of every variant on 680 random first layers (modelled over
+// measured 0.88-1.08, 5th to 95th percentile); the variant it picks ran within
+// 1% of the fastest on 95% of them and within 10% on all.
 double direct_rows_us(const ConvShape &s, const ilpm_plan &p)
 {
     const RowsVariant &d = kRows[p.variant - kFirstRows];
     const RowsArgs a = rows_args(s, d);
+    const DirectRounds r = direct_rounds(p);
     const int chunks = a.chunks16 > 0 ? a.chunks16 : a.chunks;
     const int dmas = s.c_in * s.k * chunks + ceil_div(16 * d.cw * a.kt, a.w16 ? 256 : 64) + 1;
-    return 2.95 + ceil_div(p.grid, 256) * (0.101 * dmas + 0.0198 * d.steps * d.nb);
+    const double out_mb = 4e-6 * s.c_out * s.h_out * s.w_out;
+    return 2.49 + r.one * (0.0055 * dmas + 0.0078 * d.steps * d.nb + 0.0272 * d.steps) +
+           r.full * (0.0135 * dmas + 0.0145 * d.steps * d.nb) + 0.118 * out_mb;
 }
 
-bool direct_best_rows(const ConvShape &s, ilpm_plan *p)
+// The same of the LDS-tiled VALU kernel, whose workgroups stage halos and run
+// C_in*K*K multiply-adds per lane and output channel: fitted to 425 of those
+// layers (0.90-1.12).
+double direct_lds_us(const ConvShape &s, const ilpm_plan &p)
+{
+    const DirectArgs a = make_args(s);
+    const DirectRounds r = direct_rounds(p);
+    const double q = p.grid / 256.0, kt = (double)s.c_in * s.k * s.k;
+    return 2.94 + q * (0.69 + 0.0077 * kt) + r.full * 0.0877 * kt + r.one * 0.000897 * s.c_in * a.halo_h * a.halo_w;
+}
+
+bool direct_best_rows(const ConvShape &s, ilpm_plan *p, double *us_out)
 {
     double best = 1e30;
     for (int v = kFirstRows; v < kFirstRows + kNumRows; ++v) {
@@ -760,6 +786,7 @@ bool direct_best_rows(const ConvShape &s, ilpm_plan *p)
             *p = q;
         }
     }
+    *us_out = best;
     return best < 1e30;
 }
 

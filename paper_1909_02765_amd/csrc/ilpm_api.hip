@@ -199,15 +199,20 @@ int compute_base_plan(const ConvShape &s, ilpm_plan *p, bool prepacked, bool poo
 // - Else, where the base plan is direct, the row kernel if it takes the whole
 //   contraction (C_in*K*K <= 148): 7x7 stride 2 3->64 at 224^2 22.2 us direct,
 //   9.0 by rows; 7x7 1->24 at 300^2 11.5, 10.0; 5x5 stride 2 3->41 at 26^2
-//   13.9, 5.1.
+//   13.9, 5.1 -- but where its modelled time is not at most 0.95 times the
+//   LDS-tiled direct kernel's (7x7 3->33 at 288^2 30.3 us, 32.6 by rows).
 // - Else, in place of the LDS-tiled kernel for plain calls on OIHW weights, the
 //   row kernel at K >= 5 with C_in*K*K <= 76 and at a stride with C_in*K*K <=
-//   28: those tiles stage 8 channels or more (5x5 3->64 at 224^2 12.2 us, 9.2
-//   by rows; 5x5 1->52 at 175x121 6.2, 4.7; 3x3 stride 2 3->32 at 299^2 5.8,
-//   4.9).  At a stride with more channels (3x3 8->128 at 300^2 11.9, 15.6 by
-//   rows) and for 3x3 at stride 1, whose tiles stage 4 (4->64 at 320x240 9.5,
-//   11.8 by rows), the tiled kernel is ahead.  Pooled and prepacked calls keep
-//   it too: it pools in its epilogue and reads the packed layout.
+//   28, where its modelled time is at most 0.9 times the tiled kernel's: those
+//   tiles stage 8 channels or more (5x5 3->64 at 224^2 12.2 us, 9.2 by rows;
+//   5x5 1->52 at 175x121 6.2, 4.7; 3x3 stride 2 3->32 at 299^2 5.8, 4.9), but on
+//   a small map one round of them is shorter than the rows' one chain (5x5
+//   3->23 at 117x103 4.3, 5.6 by rows; without the times 45 of 73 random 5x5
+//   layers were slower by rows).  At a stride with more channels (3x3 8->128
+//   at 300^2 11.9, 15.6 by rows) and for 3x3 at stride 1, whose tiles stage 4
+//   (4->64 at 320x240 9.5, 11.8 by rows), the tiled kernel is ahead.  Pooled and
+//   prepacked calls keep it too: it pools in its epilogue and reads the packed
+//   layout.
 int compute_plan(const ConvShape &s, ilpm_plan *p, bool prepacked, bool pooled)
 {
     bool tuned;
@@ -243,7 +248,11 @@ int compute_plan(const ConvShape &s, ilpm_plan *p, bool prepacked, bool pooled)
     const int64_t kt = (int64_t)s.c_in * s.k * s.k;
     ilpm_plan q;
     const bool small = (s.k >= 5 && kt <= 76) || (s.stride > 1 && kt <= 28);
-    if ((direct || (small && !prepacked && !pooled)) && direct_best_rows(s, &q)) *p = q;
+    double us;
+    if ((direct || (small && !prepacked && !pooled)) && direct_best_rows(s, &q, &us)) {
+        if (direct ? p->variant != 0 || us < 0.95 * direct_lds_us(s, *p) : us < 0.9 * igemm_plan_us(s, *p, false, false))
+            *p = q;
+    }
     return rc;
 }
 

@@ -23,9 +23,12 @@ bool direct_make_plan(const ConvShape &s, int variant, ilpm_plan *p);
 // chain of matrix instructions) and the largest C_in*K*K each takes.
 bool direct_is_lowc(int v);
 int direct_lowc_max_kt(int v);
-// The conv_direct_rows plan with the shortest modelled time; false where the
-// contraction C_in*K*K or the rows are too long for all of them.
-bool direct_best_rows(const ConvShape &s, ilpm_plan *p);
+// The conv_direct_rows plan with the shortest modelled time, and that time in
+// us; false where the contraction C_in*K*K or the rows are too long for all of
+// them.
+bool direct_best_rows(const ConvShape &s, ilpm_plan *p, double *us);
+// Modelled time in us of a plan of the LDS-tiled direct kernel (variant 0).
+double direct_lds_us(const ConvShape &s, const ilpm_plan &p);
 // relu: store max(conv + bias, 0).
 hipError_t direct_launch(const ilpm_plan &p, const ConvShape &s, const float *x, const float *w,
                          const float *bias, float *out, hipStream_t stream, bool relu);

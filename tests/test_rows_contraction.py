@@ -29,12 +29,15 @@ def test_contraction_limit(v):
 
 
 @pytest.mark.parametrize("shape,rows", [
-    ((3, 224, 224, 64, 7, 2, 3), True), ((1, 40, 300, 9, 11, 4, 0), True), ((3, 64, 64, 96, 5, 1, 2), True),
+    ((3, 224, 224, 64, 7, 2, 3), True), ((1, 40, 300, 9, 11, 4, 0), True), ((3, 224, 224, 64, 5, 1, 2), True),
+    ((1, 175, 121, 52, 5, 1, 2), True), ((3, 64, 64, 96, 5, 1, 2), False), ((3, 117, 103, 23, 5, 1, 2), False),
+    ((3, 11, 10, 70, 5, 1, 2), False), ((3, 38, 38, 10, 5, 1, 2), False), ((3, 104, 104, 29, 5, 1, 2), False),
     ((3, 100, 100, 32, 3, 2, 1), True), ((4, 100, 100, 32, 3, 2, 1), False), ((4, 64, 64, 64, 7, 1, 3), False),
     ((5, 64, 64, 64, 3, 1, 1), False), ((16, 64, 64, 64, 5, 2, 2), False)])
 def test_default_plan(shape, rows):
-    """Rows where the contraction fits and the LDS-tiled kernel has no 4-channel
-    stage; pooled and prepacked calls keep a plan that pools and packs."""
+    """Rows where the contraction fits, the LDS-tiled kernel has no 4-channel
+    stage and is not the faster one (5x5 3->23 at 117x103: 4.3 us tiled, 5.6 by
+    rows); pooled and prepacked calls keep a plan that pools and packs."""
     p = ilpm.plan(*shape)
     assert ("_rows_" in ilpm.variant_name(p.path, p.variant)) == rows
     if p.path == ilpm.PATH_DIRECT and rows:
@@ -107,7 +110,7 @@ def test_default_route_matches_the_direct_kernel(gpu):
     direct kernel's results are, and within rounding of it elsewhere."""
     import torch
     for i, (c_in, h, w, c_out, k, s, pad) in enumerate(
-            [(3, 50, 52, 33, 7, 2, 3), (1, 33, 47, 20, 9, 1, 4), (2, 30, 30, 70, 5, 1, 2), (3, 21, 40, 16, 3, 2, 1)]):
+            [(3, 50, 52, 33, 7, 2, 3), (1, 33, 47, 20, 9, 1, 4), (1, 30, 30, 70, 5, 1, 2), (3, 21, 40, 16, 3, 2, 1)]):
         plan = ilpm.plan(c_in, h, w, c_out, k, s, pad)
         assert "_rows_" in ilpm.variant_name(plan.path, plan.variant)
         x, wt, b = gpu.random_case(9600 + i, c_in, h, w, c_out, k)
