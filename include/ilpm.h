@@ -205,9 +205,11 @@ int ilpm_conv2d_validate(const void *in, const void *w, const void *bias,
  *                                 no matrix-core variant takes the shape);
  *   ILPM_SPLIT=n                  matrix-core plans with n input-channel
  *                                 splits;
- *   ILPM_TILE=<h>x<w>             only variants whose output tile is h x w
- *                                 (ILPM_ERR_UNSUPPORTED if none takes the
- *                                 shape).
+ *   ILPM_TILE=<h>x<w>             only plans whose output tile is h x w
+ *                                 (ILPM_ERR_UNSUPPORTED if there is none for
+ *                                 the shape).
+ * The bf16-split plans take part in all of them; the row kernels are planned
+ * without overrides only.
  */
 int ilpm_conv2d_plan(int C_in, int H, int W, int C_out, int K, int stride, int pad,
                      ilpm_plan *plan);

@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <vector>
 
@@ -128,6 +129,13 @@ int validate(const void *in, const void *w, const void *bias, const ConvShape &s
     return ILPM_OK;
 }
 
+// Whether a plan has the output tile that an override asks for, if any does.
+bool tile_ok(const ilpm_plan &q)
+{
+    const Overrides &o = overrides();
+    return o.tile_h == 0 || (q.tile_h == o.tile_h && q.tile_w == o.tile_w);
+}
+
 // The default plan: the measured best for this exact shape when a tuning
 // table has it -- the table of this weight layout and epilogue first, then
 // (pooled) the plain table of the same layout, then the OIHW tables -- else
@@ -148,7 +156,6 @@ int compute_base_plan(const ConvShape &s, ilpm_plan *p, bool prepacked, bool poo
         if (tuned_plan(s, p, false, false)) return ILPM_OK;
         *tuned = false;
     }
-    auto tile_ok = [&](const ilpm_plan &q) { return o.tile_h == 0 || (q.tile_h == o.tile_h && q.tile_w == o.tile_w); };
     if (o.path != ILPM_PATH_DIRECT) {
         bool found = false;
         double best = 0;
@@ -218,21 +225,26 @@ int compute_plan(const ConvShape &s, ilpm_plan *p, bool prepacked, bool pooled)
     bool tuned;
     const int rc = compute_base_plan(s, p, prepacked, pooled, &tuned);
     const Overrides &o = overrides();
-    if (tuned || o.path >= 0 || o.splits > 0 || o.tile_h > 0) return rc;
+    if (tuned || o.path == ILPM_PATH_DIRECT) return rc;
     const bool direct = rc == ILPM_OK && p->path == ILPM_PATH_DIRECT;
     if (direct && direct_is_lowc(p->variant)) return rc;
-    if (s.c_in >= 16 && rc == ILPM_OK) {
+    // (Without a base plan, where an override leaves none, unsplit.)
+    if (s.c_in >= 16 || rc != ILPM_OK) {
         const ilpm_plan base = *p;
-        const bool base_pools = !direct && igemm_pools(base);
-        const size_t room = direct || base.splits == 1 ? 0 : std::min(base.workspace_bytes, ILPM_NOALLOC_SCRATCH_BYTES);
-        double best = direct ? 1e30 : 0.9 * igemm_plan_us(s, base, prepacked, pooled);
+        const bool has_base = rc == ILPM_OK && !direct;
+        const bool base_pools = has_base && igemm_pools(base);
+        const size_t room = o.splits > 0 ? ILPM_NOALLOC_SCRATCH_BYTES
+                            : has_base && base.splits > 1 ? std::min(base.workspace_bytes, ILPM_NOALLOC_SCRATCH_BYTES)
+                                                          : 0;
+        const std::initializer_list<int> any_splits = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}, forced = {o.splits};
+        double best = has_base ? 0.9 * igemm_plan_us(s, base, prepacked, pooled) : 1e30;
         bool found = false;
         for (int v = 0; v < igemm_num_variants(); ++v) {
             bool even;
             if (!igemm_is_split(v, &even) || (even && !pooled && !base_pools) || (!even && base_pools)) continue;
-            for (int splits : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
+            for (int splits : o.splits > 0 ? forced : any_splits) {
                 ilpm_plan q;
-                if (!igemm_make_plan(s, v, splits, &q) || q.splits != splits) continue;
+                if (!igemm_make_plan(s, v, splits, &q) || q.splits != splits || !tile_ok(q)) continue;
                 if (q.workspace_bytes > room) continue;
                 const double us = igemm_plan_us(s, q, prepacked, pooled);
                 if (us < best) {
@@ -244,6 +256,7 @@ int compute_plan(const ConvShape &s, ilpm_plan *p, bool prepacked, bool pooled)
         }
         if (found) return ILPM_OK;
     }
+    if (o.path >= 0 || o.splits > 0 || o.tile_h > 0) return rc;
     if (rc != ILPM_OK) return rc;
     const int64_t kt = (int64_t)s.c_in * s.k * s.k;
     ilpm_plan q;

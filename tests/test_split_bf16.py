@@ -115,6 +115,25 @@ def test_fp32_plans_stay_where_they_are_faster(shape, fp32, split):
     assert p.path == ilpm.PATH_IGEMM and p.variant not in SPLIT
 
 
+def test_overrides_take_the_split_variants():
+    """The environment overrides narrow all matrix-core variants, bf16-split ones
+    among them: the matrix-core family alone takes 1x1 filters with a stride
+    (that only they run), plans the headline layer as it does by itself, and
+    splits and tiles are those asked for."""
+    from test_abi import plans_with_env
+    strided, early, deep = (256, 56, 56, 512, 1, 2, 0), (64, 224, 224, 64, 3, 1, 1), (320, 71, 97, 144, 3, 1, 1)
+    default = plans_with_env({}, [early])
+    got = plans_with_env({"ILPM_FORCE_PATH": "igemm"}, [strided, early])
+    assert got[0]["path"] == ilpm.PATH_IGEMM and "_b3_" in got[0]["name"] and got[0]["splits"] == 1
+    assert got[1] == default[0] and "_b3_" in got[1]["name"]
+    got = plans_with_env({"ILPM_SPLIT": "2"}, [strided, deep])
+    assert all(g["splits"] == 2 for g in got) and "_b3_" in got[0]["name"]
+    got = plans_with_env({"ILPM_TILE": "8x32"}, [early])
+    assert got[0]["tile"] == [8, 32] and "_b3_" in got[0]["name"]
+    got = plans_with_env({"ILPM_FORCE_PATH": "direct"}, [strided, early])
+    assert all(g["path"] == ilpm.PATH_DIRECT for g in got)
+
+
 @pytest.fixture
 def gpu():
     import gpu_common
