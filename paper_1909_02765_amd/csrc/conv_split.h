@@ -19,9 +19,9 @@
 //
 // Two limits of the split, and what is done about them.  A value whose bf16
 // rounding overflows, an infinity or a NaN gives NaN parts, so every output
-// it touches is not finite; such outputs are computed again with plain fp32
-// FMAs before they are stored (at the kernel's end), which gives what the fp32
-// kernels give.  And bf16 ends at 2^-133: a value below 2^-109 in magnitude keeps an
+// it touches is not finite; such outputs are computed again with fp32 matrix
+// instructions before they are stored (at the kernel's end), which gives what
+// the fp32 kernels give.  And bf16 ends at 2^-133: a value below 2^-109 in magnitude keeps an
 // absolute error of at most 2^-134.
 //
 // GEMM view: rows = output channels, columns = output pixels, contraction =
@@ -675,47 +675,110 @@ __global__ __launch_bounds__(C::NT, C::WPE) void conv_split(const float *__restr
                 for (int r = 0; r < 4; ++r) sum0 = __builtin_fmaf(sum[e][m][r], 0.f, sum0);
 
     // A value that is not finite: an infinity, a NaN or a value near the top
-    // of the range among its operands, or a true overflow.  Compute it again
-    // with fp32 FMAs.  (Through this wave's own LDS slots, so that the cold
-    // loop indexes memory and not registers.)
-    if (__builtin_amdgcn_ballot_w64(sum0 != 0.f || sum0 != sum0) != 0) {
-        floatx4 *const own = red + (wave * 64 + lane) * C::MA;
+    // of the range among its operands, or a true overflow.  Compute its 32x32
+    // block again with fp32 matrix instructions from memory, a lane's half
+    // taking every other input channel, and keep what is finite.  (All of a
+    // wave's blocks together, the loads of a batch of products flying while the
+    // batch before multiplies.  64->64 at 224^2: finite 27 us a call, one NaN
+    // pixel 65, NaN everywhere 104; 256->256 at 56^2 31, 317 and 359.  By single
+    // lanes over C_in*K*K these were 1579 and 3479, 1868 and 3392 us.)
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(sum0 != 0.f || sum0 != sum0) != 0, 0)) {
+        constexpr int CB = C::KS == 1 ? 4 : 1, KH = C::KS == 5 ? 1 : C::KS, BATCH = CB * KH * C::KS;
+        const __amdgpu_buffer_rsrc_t rx = make_rsrc(x, (unsigned)a.c_in * plane4);
+        const __amdgpu_buffer_rsrc_t rw = PK ? make_rsrc(w_packed, (unsigned)a.nchunks * (C::COT * C::ROW * 4u))
+                                             : make_rsrc(w, (unsigned)a.c_out * wrow * 4u);
+        const int ci_end = min(c_end * C::CC, a.c_in);
+        int ih0[C::NB], iw0[C::NB];
 #pragma unroll
-        for (int e = 0; e < C::ITEMS; ++e) {
-            if (e % C::WK != wk) continue;
+        for (int b = 0; b < C::NB; ++b) {
+            int pr, pc;
+            slot_pixel<POOL>((wp * C::NB + b) * 32 + l32, t, pr, pc);
+            ih0[b] = (oh0 + pr) * stride - a.pad;
+            iw0[b] = (ow0 + pc) * stride - a.pad;
+        }
 #pragma unroll
-            for (int m = 0; m < C::MA; ++m) own[m] = sum[e][m];
-#pragma unroll 1
-            for (int i = 0; i < 4 * C::MA; ++i) {
-                const int r = i & 3, m = i >> 2;
-                float *const at = reinterpret_cast<float *>(own + m) + r;
-                const int co_l = el_co(e, m, r), co = co0 + co_l;
-                int pr, pc;
-                const int slot = el_slot(e, r);
-                slot_pixel<POOL>(slot, t, pr, pc);
-                if (!not_finite(*at) || slot >= t.th * t.tw || co >= a.c_out || oh0 + pr >= a.h_out ||
-                    ow0 + pc >= a.w_out)
-                    continue;
-                float acc = with_bias ? bias[co] : 0.f;
-#pragma unroll 1
-                for (int ci = c_begin * C::CC; ci < min(c_end * C::CC, a.c_in); ++ci)
-#pragma unroll 1
-                    for (int tap = 0; tap < C::KK; ++tap) {
-                        const int ih = (oh0 + pr) * stride - a.pad + tap / C::KS;
-                        const int iw = (ow0 + pc) * stride - a.pad + tap % C::KS;
-                        const float xv = ih >= 0 && ih < a.h && iw >= 0 && iw < a.w
-                                             ? x[((size_t)ci * a.h + ih) * a.w + iw] : 0.f;
-                        const int cl = ci % C::CC;
-                        const float wv = PK ? w_packed[(size_t)(ci / C::CC) * (C::COT * C::ROW) +
-                                                       (((tap * C::C8 + cl / 8) * 2 + cl % 8 / 4) * C::COT + co_l) * 4 +
-                                                       cl % 4]
-                                            : w[(size_t)co * wrow + (size_t)ci * C::KK + tap];
-                        acc = __builtin_fmaf(xv, wv, acc);
+        for (int m = 0; m < C::MA; ++m) {
+            bool redo[C::NB];
+            floatx16 acc[C::NB];
+#pragma unroll
+            for (int b = 0; b < C::NB; ++b) {
+                bool bad = false;
+#pragma unroll
+                for (int e = 4 * b; e < 4 * b + 4; ++e)
+                    if (e % C::WK == wk)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            bad |= not_finite(sum[e][m][r]) && s_out[el_slot(e, r)] >= 0 &&
+                                   co0 + el_co(e, m, r) < a.c_out;
+                redo[b] = __builtin_amdgcn_ballot_w64(bad) != 0;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int co = co0 + el_co(r / 4, m, r % 4);
+                    acc[b][r] = with_bias && co < a.c_out ? bias[co] : 0.f;
+                }
+            }
+            const int co_l = (wc * C::MA + m) * 32 + l32;
+            // Batch (ci0, kh0): channels ci0 + 2*cb + g, rows kh0 .. of the filter.
+            float xv[C::NB][BATCH], wv[BATCH], xn[C::NB][BATCH], wn[BATCH];
+            auto load = [&](int ci0, int kh0) {
+#pragma unroll
+                for (int j = 0; j < BATCH; ++j) {
+                    const int ci = ci0 + j / (KH * C::KS) * 2 + g;
+                    const int kh = kh0 + j / C::KS % KH, kw = j % C::KS, tap = kh * C::KS + kw;
+                    const int cl = ci % C::CC;
+                    unsigned wo = 0x80000000u;
+                    if (PK) {
+                        if (ci < ci_end)
+                            wo = (unsigned)(ci / C::CC * (C::COT * C::ROW) +
+                                            (((tap * C::C8 + cl / 8) * 2 + cl % 8 / 4) * C::COT + co_l) * 4 + cl % 4) *
+                                 4u;
+                    } else {
+                        if (ci < ci_end && co0 + co_l < a.c_out)
+                            wo = ((unsigned)(co0 + co_l) * wrow + (unsigned)(ci * C::KK + tap)) * 4u;
                     }
-                *at = acc;
+                    wn[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rw, (int)wo, 0, 0));
+#pragma unroll
+                    for (int b = 0; b < C::NB; ++b)
+                        if (redo[b]) {
+                            const int ih = ih0[b] + kh, iw = iw0[b] + kw;
+                            const bool in = ci < ci_end && ih >= 0 && ih < a.h && iw >= 0 && iw < a.w;
+                            const unsigned xo =
+                                in ? (unsigned)ci * plane4 + (unsigned)(ih * a.w + iw) * 4u : 0x80000000u;
+                            xn[b][j] =
+                                __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rx, (int)xo, 0, 0));
+                        }
+                }
+            };
+            int ci0 = c_begin * C::CC, kh0 = 0;
+            load(ci0, kh0);
+#pragma unroll 1
+            while (ci0 < ci_end) {
+#pragma unroll
+                for (int j = 0; j < BATCH; ++j) {
+                    wv[j] = wn[j];
+#pragma unroll
+                    for (int b = 0; b < C::NB; ++b) xv[b][j] = xn[b][j];
+                }
+                kh0 += KH;
+                if (kh0 >= C::KS) {
+                    kh0 = 0;
+                    ci0 += 2 * CB;
+                }
+                load(ci0, kh0);  // (past the last channel: zeros)
+#pragma unroll
+                for (int b = 0; b < C::NB; ++b)
+                    if (redo[b])
+#pragma unroll
+                        for (int j = 0; j < BATCH; ++j)
+                            acc[b] = POOL ? __builtin_amdgcn_mfma_f32_32x32x2f32(xv[b][j], wv[j], acc[b], 0, 0, 0)
+                                          : __builtin_amdgcn_mfma_f32_32x32x2f32(wv[j], xv[b][j], acc[b], 0, 0, 0);
             }
 #pragma unroll
-            for (int m = 0; m < C::MA; ++m) sum[e][m] = own[m];
+            for (int e = 0; e < C::ITEMS; ++e)
+                if (e % C::WK == wk && redo[e / 4])
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (not_finite(sum[e][m][r])) sum[e][m][r] = acc[e / 4][e % 4 * 4 + r];
         }
     }
 

@@ -205,6 +205,76 @@ def test_values_that_are_not_finite(gpu, v):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("v", [v for v in SPLIT if _name(v).endswith("_even")], ids=_name)
+def test_pooled_values_that_are_not_finite(gpu, v):
+    """The same values through the 2x2 max-pool in the kernel, on both weight
+    layouts: the bits of the unpooled result of the same plan, ReLU and the
+    windows taken in the kernels' order (a NaN stays only as a window's first)."""
+    import torch
+    info = ilpm.variant_info(ilpm.PATH_IGEMM, v)
+    k, s = info["k"], info["stride"]
+    c_in, c_out = 2 * info["ci_chunk"] + 5, info["co_tile"] + 3
+    x, wt, b = gpu.random_case(9450, c_in, 30, 34, c_out, k)
+    x[0, 3, 4, 5], x[0, 7, 9, 9], x[0, 8, 2, 2], x[0, c_in - 1, 22, 23] = np.inf, np.nan, 3.4e38, -np.inf
+    x[0, 2, 16, 16] = np.nan  # a window's first, of 1x1 filters too
+    wt[5, 2] = -np.inf
+    xd, wd, bd = gpu.dev(x), gpu.dev(wt), gpu.dev(b)
+    plan = ilpm.plan_variant(c_in, 30, 34, c_out, k, s, k // 2, ilpm.PATH_IGEMM, v, 1)
+    packed = ilpm.prepack_weights(wd, plan)
+    gpu.note(f"[split pooled not finite] {_name(v)}")
+    epi = ilpm.EPI_RELU | ilpm.EPI_MAXPOOL2
+    full = ilpm.conv2d(xd, wd, bd, s, k // 2, plan=plan).cpu().numpy()
+    got = ilpm.conv2d_epilogue(xd, wd, bd, s, k // 2, epi, plan=plan)
+    got_packed = ilpm.conv2d_prepacked_epilogue(xd, packed, c_out, k, bd, s, k // 2, epi, plan=plan)
+    torch.cuda.synchronize()
+    ho, wo = full.shape[2] // 2 * 2, full.shape[3] // 2 * 2
+    windows = [full[:, :, i:ho:2, j:wo:2] for i in (0, 1) for j in (0, 1)]
+    want = windows[0]
+    with np.errstate(invalid="ignore"):
+        for q in windows[1:]:
+            want = np.where(q > want, q, want)
+        want = np.where(want < 0, np.float32(0), want)
+    assert np.isnan(want).any() and np.isinf(want).any()
+    np.testing.assert_array_equal(got.cpu().numpy(), want)
+    np.testing.assert_array_equal(got_packed.cpu().numpy(), want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(64, 224, 224, 64, 3, 1, 1), (512, 60, 60, 256, 1, 1, 0), (96, 90, 90, 64, 5, 2, 2)], ids=str)
+def test_values_that_are_not_finite_cost_no_more_than_a_few_calls(gpu, shape):
+    """One NaN pixel, and NaN everywhere: the outputs they reach are computed
+    again, in at most 20 times a finite call's time (measured 2 to 8; by single
+    lanes it was more than 100)."""
+    import torch
+    c_in, h, w, c_out, k, s, pad = shape
+    plan = ilpm.plan(*shape)
+    assert plan.variant in SPLIT
+    x, wt, b = gpu.random_case(9600, c_in, h, w, c_out, k)
+    xd, wd, bd = gpu.dev(x), gpu.dev(wt), gpu.dev(b)
+    one = xd.clone()
+    one[0, 3, h // 2, w // 2] = float("nan")
+    out = ilpm.conv2d(xd, wd, bd, s, pad)
+
+    def us(t):
+        times = []
+        for _ in range(10):
+            e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            e0.record()
+            for _ in range(4):
+                ilpm.conv2d(t, wd, bd, s, pad, out=out)
+            e1.record()
+            torch.cuda.synchronize()
+            times.append(e0.elapsed_time(e1) * 250.0)
+        return sorted(times)[5]
+
+    for _ in range(3):
+        us(xd)
+    finite, single, every = us(xd), us(one), us(torch.full_like(xd, float("nan")))
+    gpu.note(f"[split not finite, time] {shape}: finite {finite:.1f} us, one NaN {single:.1f}, all NaN {every:.1f}")
+    assert single < 20 * finite and every < 20 * finite
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("shape", [(388, 15, 16, 399, 3, 1, 1), (208, 21, 23, 224, 1, 2, 0), (144, 61, 68, 32, 5, 1, 2),
                                    (44, 84, 84, 52, 5, 2, 2)], ids=str)
 def test_unsplit_shapes_need_no_workspace(gpu, shape):
