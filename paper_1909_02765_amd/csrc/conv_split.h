@@ -296,7 +296,10 @@ __global__ __launch_bounds__(C::NT, C::WPE) void conv_split(const float *__restr
     // The input from a chunk on; for chunks past this split's last one an
     // empty range (the loads are issued all the same, read zeros and touch no
     // memory: with the same loads in flight on every path the compiler's waits
-    // for them are exact).
+    // for them are exact.  Where the last stage is compiled on its own, its
+    // pixel loads, whose values nothing reads, go; its weight DMA, of an empty
+    // range too, may then still be in flight after it, so nothing may use the
+    // weight buffers again).
     auto chunk_rsrc = [&](int chunk) {
         const int ci0 = chunk * C::CC;
         return make_rsrc(x + (size_t)ci0 * (plane4 / 4u), chunk < c_end ? (unsigned)(a.c_in - ci0) * plane4 : 0u);
@@ -575,7 +578,12 @@ __global__ __launch_bounds__(C::NT, C::WPE) void conv_split(const float *__restr
             const int noff = px_off(following());
             step(std::integral_constant<int, J1 - J0>{}, std::integral_constant<int, J0>{}, xc, xn, off, noff, fx, fw,
                  nw, wv, [&](int b) {
-                     if (I == 0) dma_w(wn, chunk + 1, b * C::WJ / C::NB, (b + 1) * C::WJ / C::NB);
+                     if (I == 0) {
+                         dma_w(wn, chunk + 1, b * C::WJ / C::NB, (b + 1) * C::WJ / C::NB);
+                         // stage_ready_keep_lds counts on the pixel loads following:
+                         // no memory instruction passes here.
+                         __builtin_amdgcn_sched_barrier(0x48f);
+                     }
                      if (b == C::NB - 1 && J1 > J0) {
                          const __amdgpu_buffer_rsrc_t rx = chunk_rsrc(chunk + 2);
 #pragma unroll
