@@ -2,7 +2,8 @@
 // (v_mfma_f32_32x32x16_bf16).
 //
 // gfx950's bf16 matrix instructions do 16 times the multiply-adds of its fp32
-// ones per cycle.  An fp32 value is the sum of three bf16 values,
+// ones per cycle.  An fp32 value of 2^-109 and more is the sum of three bf16
+// values,
 //   h = bf16(x), m = bf16(x - h), l = bf16(x - h - m),
 // exactly (24 significand bits in three parts of 8, each rounded to nearest,
 // so each remainder has a sign of its own), and a product x*w is
@@ -12,17 +13,21 @@
 // product has an accumulator of its own (the five small ones, 2^-8 and less of
 // it, share another): the rounding of the accumulation is then that of one
 // addition per 16 terms where the fp32 instructions round once per term.
-// Measured against 64 bits, chains of 288 to 12800 terms: 0.3 times the
-// 2-norm error of the v_mfma_f32_16x16x4_f32 chain (576 terms 1.3e-7 against
-// 4.3e-7, 12800 terms 7.2e-7 against 2.1e-6); with one accumulator for all six
-// products, 0.85 times and a bias of a third of that.
+// Measured against 64 bits, 2-norm, against the fp32 kernels that ran the layer
+// before: 0.3 times their error on 3x3 64->64 at 224^2 (1.4e-7, 4.5e-7) and
+// 128->128 at 112^2, 0.4 on 64->96 at 301x403 and 75->150 at 61x45, 0.55 on 1x1
+// 256->128 at 56^2; one chain of 12800 terms 7.2e-7 against 2.1e-6.  (With one
+// accumulator for all six products 0.85 times and a bias of a third of that.)
 //
 // Two limits of the split, and what is done about them.  A value whose bf16
 // rounding overflows, an infinity or a NaN gives NaN parts, so every output
 // it touches is not finite; such outputs are computed again with fp32 matrix
 // instructions before they are stored (at the kernel's end), which gives what
-// the fp32 kernels give.  And bf16 ends at 2^-133: a value below 2^-109 in magnitude keeps an
-// absolute error of at most 2^-134.
+// the fp32 kernels give.  And bf16 ends at 2^-133: a value below 2^-109 in
+// magnitude keeps an absolute error of at most 2^-134, which ilpm.h states.
+// (Both operands scaled by 2^24 at their splitting, two multiplications a pair
+// and the outputs scaled back, would keep all bits of every value; it made the
+// measured layers 2-7% slower.)
 //
 // GEMM view: rows = output channels, columns = output pixels, contraction =
 // input channels x taps: a store instruction then writes 32 consecutive pixels
@@ -46,10 +51,11 @@
 // 16x16x32 instruction takes four units a step: 18 of them in 5 steps).  For
 // each step a wave reads its weights (8 per lane) two steps ahead, splits them
 // during the step before and runs all its pixel blocks with them.  Splitting
-// the weights at their use costs 44 VALU instructions per step, beside its 24
-// matrix instructions of 32 cycles, where they are nearly free (a burst of
-// them before the matrix instructions is not), and as many times over as waves
-// share an output channel; splitting them once on the way into LDS measured
+// the weights at their use costs 44 VALU instructions per step, placed one by
+// one beside its 6*NB matrix instructions of 32 cycles (NB = 1 to 4 pixel
+// blocks; a burst of them before the matrix instructions costs more), and as
+// many times over as waves share an output channel: a quarter to a third of a
+// 3x3 stage; splitting them once on the way into LDS measured
 // slower: a serial phase per stage of 1.5 us (prepacked) to 3.3 us (OIHW,
 // through a transposition in LDS) against 1.9 us of matrix work, which two
 // workgroups per compute unit, in step with each other, did not hide.

@@ -205,6 +205,29 @@ def test_values_that_are_not_finite(gpu, v):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("v", [v for v in SPLIT if not _name(v).endswith("_even")], ids=_name)
+def test_small_values(gpu, v):
+    """Inputs, or weights, scaled by 2^-90 to 2^-140: bf16 ends at 2^-133, so
+    below 2^-109 an operand keeps an absolute error of 2^-134, and above it 24
+    bits.  Per product |x||w| then at most 2^-22 of it (operands and dropped
+    parts), 2^-134 of the other operand and, per addition, 2^-149."""
+    info = ilpm.variant_info(ilpm.PATH_IGEMM, v)
+    k, s = info["k"], info["stride"]
+    x, wt, _ = gpu.random_case(9700, 40, 18, 21, info["co_tile"], k)
+    ones_x, ones_w = np.ones_like(x), np.ones_like(wt)
+    plan = ilpm.plan_variant(40, 18, 21, info["co_tile"], k, s, k // 2, ilpm.PATH_IGEMM, v, 1)
+    for log2 in (-90, -108, -115, -120, -130, -140):
+        for xs, ws in ((x * np.float32(2.0 ** log2), wt), (x, wt * np.float32(2.0 ** log2))):
+            gpu.note(f"[split small values] {_name(v)} 2^{log2}")
+            got = gpu.run_conv(xs, ws, None, s, k // 2, plan=plan).astype(np.float64)
+            ref, sab = oracle.conv2d_f64(xs, ws, None, s, k // 2)
+            other = 2.0 ** -134 * (oracle.conv2d_f64(np.abs(xs), ones_w, None, s, k // 2)[0] +
+                                   oracle.conv2d_f64(ones_x, np.abs(ws), None, s, k // 2)[0])
+            bound = sab.reshape(ref.shape) * 2.0 ** -20 + other + 40 * k * k * 2.0 ** -149
+            assert np.all(np.abs(got.reshape(ref.shape) - ref) <= bound), f"2^{log2}"
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("v", [v for v in SPLIT if _name(v).endswith("_even")], ids=_name)
 def test_pooled_values_that_are_not_finite(gpu, v):
     """The same values through the 2x2 max-pool in the kernel, on both weight
