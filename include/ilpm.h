@@ -162,7 +162,8 @@ int ilpm_set_workspace(void *ptr, size_t bytes, hipStream_t stream);
  *                         sums the tile's slices; one launch per call.
  *   ILPM_SPLIT_SUM_KERNEL a second kernel sums all slices after the first.
  * Both add the slices in split order, so their outputs are bit-identical.
- * The 2x2 max-pool epilogue always uses the second kernel.  Returns
+ * The 2x2 max-pool epilogue, bf16-split plans and plans whose tiles leave each
+ * thread more than a few partial values always use the second kernel.  Returns
  * ILPM_ERR_INVALID_ARG for any other mode.  Host only.
  */
 #define ILPM_SPLIT_SUM_FUSED 0
